@@ -140,7 +140,8 @@ template <> struct Codec<ST_F32> {
 //       (equal for both fluids: the phases' alphas make rho0_k (1 - alpha_k)
 //       the same, Sec. 2.1.1).
 // Decoding: N_i = m_c + q 2^-12 max(rho0), N^r_i = g N_i, N^b_i = (1 - g) N_i
-// (one fused multiply-add from N_i).
+// (one fused multiply-add from N_i); a node's colour masses are the exact FP64
+// sums sum_i N^r_i and sum_i N_i - sum_i N^r_i plus the rest populations.
 // The colour-blind population, which carries mass and momentum, is held as a
 // small deviation with FP16's relative precision in bulk and interface nodes
 // alike, and the colour split with a uniform 1.5e-5 quantum; a per-colour
@@ -166,9 +167,11 @@ __device__ __forceinline__ uint32_t mix32(uint32_t h)
     h ^= h >> 16;
     return h;
 }
-// j-th dither of a node: a Weyl sequence (golden-ratio increments) from the
-// node's hashed seed; its high bits are the ones used, and they spread evenly
-__device__ __forceinline__ uint32_t weyl(uint32_t seed, int j) { return seed + (uint32_t)j * 0x9e3779b9u; }
+// j-th dither of a node: a Weyl sequence from the node's hashed seed whose
+// increment is the golden ratio in its high and in its low 16 bits, so that
+// either half spreads evenly: one word dithers a pair (the high bits its
+// deviation, the low 16 its share)
+__device__ __forceinline__ uint32_t weyl(uint32_t seed, int j) { return seed + (uint32_t)j * 0x9e379e37u; }
 
 typedef _Float16 cg_h2 __attribute__((ext_vector_type(2)));
 typedef __bf16 cg_b2 __attribute__((ext_vector_type(2)));
@@ -243,51 +246,63 @@ __device__ __forceinline__ void dec_pair(const SlotDesc &S, int c, uint16_t q, u
     split(N, u, nr, nb);
 }
 
-// Encode a pair; returns the decoded values the store leaves behind.
-// rnd: dither (high bits for the deviation, low 16 bits for the share);
-// sr = false: round to nearest.
-template <int ST>
-__device__ __forceinline__ void enc_pair(const SlotDesc &S, int c, float vr, float vb, uint32_t rg, uint32_t rq, bool sr,
-                                         uint16_t &q, uint16_t &u, float &nr, float &nb)
+// Share of a pair as 16.16 fixed point (65535 << 16 for a share of 1), dithered
+// by a word's low 16 bits (sr = false: rounded to nearest); u = its high half.
+// 0 and 65535 << 16 keep their high half under any dither.
+constexpr float kShareOne = 65535.f * 65536.f;
+__device__ __forceinline__ uint32_t dither_share(uint32_t t, uint32_t rnd, bool sr)
 {
-    const float n = vr + vb;
-    float g = vr * __builtin_amdgcn_rcpf(n);
-    g = g > 0.f ? (g < 1.f ? g : 1.f) : 0.f;          // NaN -> 0 (its N stays NaN)
-    g = vb == 0.f ? 1.f : (vr == 0.f ? 0.f : g);       // an absent colour stays exactly absent
-    // dither in [0, 1) from the top 23 bits (as the mantissa of a number in [1, 2))
-    const float dith = sr ? __uint_as_float(0x3f800000u | (rg >> 9)) - 1.f : 0.5f;
-    const uint32_t ui = (uint32_t)__builtin_fmaf(g, 65535.f, dith);   // g in [0,1]: 0 .. 65535
-    u = (uint16_t)(ui > 65535u ? 65535u : ui);
+    return t + (sr ? rnd & 0xffffu : 0x8000u);
+}
+// float share times kShareOne to fixed point: clamped to [0, 1]; NaN gives 0
+__device__ __forceinline__ uint32_t fix_share(float ts) { return (uint32_t)__builtin_amdgcn_fmed3f(ts, 0.f, kShareOne); }
+
+// Encode a pair given its colour-blind population n and its undithered share
+// (fix_share); N, nr: the colour-blind and red populations that the store
+// leaves behind.  rnd: dither (high bits for the deviation, low 16 for the
+// share); sr = false: round to nearest.
+template <int ST>
+__device__ __forceinline__ void enc_pair(const SlotDesc &S, int c, float n, uint32_t t, uint32_t rnd, bool sr, uint16_t &q,
+                                         uint16_t &u, float &N, float &nr)
+{
+    u = (uint16_t)(dither_share(t, rnd, sr) >> 16);
     const float x = (n - S.mref[c]) * S.dscale;
-    q = sr ? Codec<ST>::enc_q(x, rq) : Codec<ST>::enc_q_nearest(x);
-    split(__builtin_fmaf(Codec<ST>::dec_q(q), S.dmul, S.mref[c]), u, nr, nb);
+    q = sr ? Codec<ST>::enc_q(x, rnd) : Codec<ST>::enc_q_nearest(x);
+    N = __builtin_fmaf(Codec<ST>::dec_q(q), S.dmul, S.mref[c]);
+    nr = share(u) * N;
+}
+// Share of a pair of populations; an absent colour stays exactly absent.
+__device__ __forceinline__ uint32_t pair_share(float vr, float vb)
+{
+    const uint32_t t = fix_share(vr * __builtin_amdgcn_rcpf(vr + vb) * kShareOne);
+    return vb == 0.f ? (uint32_t)kShareOne : (vr == 0.f ? 0u : t);
 }
 
 // FP32 rest population of a colour: the value itself or its deviation from
 // rest0, whichever is smaller in magnitude (finer FP32 quantum for a minority
 // and for a majority colour alike); the mantissa's last bit tells which.  The
 // value is rounded onto the FP32 numbers that carry that last bit (a grid of
-// two ulps), stochastically with the dither r01 in [0, 1) (0.5: to nearest):
+// two ulps), stochastically with the 30 high bits of rnd (half: to nearest):
 // forcing the bit onto a rounded value would bias the rest, and with it the
-// colour mass, at every node and step.
-__device__ __forceinline__ uint32_t enc_rest(double v, float ref, double r01)
+// colour mass, at every node and step.  The rounding is integer arithmetic on
+// the FP64 bits: an FP32 ulp is 2^29 there, so adding 30 random bits to the
+// offset from the grid and truncating rounds up with the right probability.
+constexpr uint32_t kRestHalf = 0x80000000u;
+__device__ __forceinline__ uint32_t enc_rest(double v, float ref, uint32_t rnd)
 {
-    const uint32_t flag = fabs(v - (double)ref) < fabs(v) ? 1u : 0u;
-    const double t = flag ? v - (double)ref : v;
-    const double a = fabs(t);
-    const uint32_t m = __float_as_uint((float)a);
-    uint32_t lo, hi;
-    if ((m & 1u) == flag) {
-        if ((double)__uint_as_float(m) <= a) { lo = m; hi = m + 2u; }
-        else { lo = m - 2u; hi = m; }
-    } else {
-        lo = m - 1u;
-        hi = m + 1u;
-    }
-    if (lo > hi) lo = flag;   // below the smallest magnitude of the grid
-    const double vlo = (double)__uint_as_float(lo), vhi = (double)__uint_as_float(hi);
-    const uint32_t mm = (a - vlo) > r01 * (vhi - vlo) ? hi : lo;
-    return mm | (t < 0.0 ? 0x80000000u : 0u);
+    const double dev = v - (double)ref;
+    const bool fl = fabs(dev) < fabs(v);
+    const uint64_t bits = (uint64_t)__double_as_longlong(fl ? dev : v);
+    const uint32_t flag = fl ? 1u : 0u;
+    const uint32_t hi = (uint32_t)(bits >> 32) & 0x7fffffffu, sign = (uint32_t)(bits >> 32) & 0x80000000u;
+    const uint64_t a = ((uint64_t)hi << 32) | (uint32_t)bits;
+    const uint64_t g = a + (uint64_t)(rnd >> 2) - ((uint64_t)flag << 29);
+    uint32_t m = ((uint32_t)(g >> 29) - (896u << 23)) & ~1u;   // exponent bias 1023 -> 127
+    // below the normal FP32 range: the smallest magnitude of the grid; beyond
+    // it (only after the lattice has gone non-finite): infinity or NaN
+    if (hi - 0x38100000u >= 0x47e00000u - 0x38100000u)
+        m = hi < 0x38100000u ? 0u : __float_as_uint((float)__longlong_as_double((long long)a)) & ~1u;
+    return m | flag | sign;
 }
 // decoded rest population (FP32) and its exact value (FP64)
 __device__ __forceinline__ float dec_rest(uint32_t b, float ref, double &exact)
@@ -658,36 +673,29 @@ __device__ __forceinline__ Node finish(const SlotDesc &S, const Raw18<ST> &raw, 
     using C = Codec<ST>;
     Node nd;
     double rho[2];   // colour masses, exact (nine FP32 values sum exactly in FP64)
-    float kn[2];
     if constexpr (rest32<ST>()) {
         const float r0 = dec_rest(raw.r0[0], S.rest0[0], rho[0]);
         const float b0 = dec_rest(raw.r0[1], S.rest0[1], rho[1]);
         nd.n[0] = r0 + b0;
-        kn[0] = r0;
-        kn[1] = b0;
+        double sn = 0.0, sr = 0.0;
 #pragma unroll
         for (int i = 1; i < 9; ++i) {
-            float N, nr, nb;
-            dec_pair<ST>(S, vclass(i), raw.v[i], raw.v[9 + i], N, nr, nb);
+            const float N = __builtin_fmaf(C::dec_q(raw.v[i]), S.dmul, S.mref[vclass(i)]);
+            const float nr = share(raw.v[9 + i]) * N;
             nd.n[i] = N;
-            rho[0] += (double)nr;
-            rho[1] += (double)nb;
-            if (cx(i) >= 0) {   // the six populations that come from x-1 or x
-                kn[0] += nr;
-                kn[1] += nb;
-            }
+            sn = i == 1 ? (double)N : sn + (double)N;
+            sr = i == 1 ? (double)nr : sr + (double)nr;
         }
+        rho[0] += sr;
+        rho[1] += sn - sr;
     } else {
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            rho[k] = 0.0;
-            kn[k] = 0.f;
 #pragma unroll
             for (int i = 0; i < 9; ++i) {
                 const float v = C::dec(raw.v[k * 9 + i], S, k, vclass(i));
-                rho[k] += (double)v;
+                rho[k] = i == 0 ? (double)v : rho[k] + (double)v;
                 nd.n[i] = (k == 0) ? v : nd.n[i] + v;
-                if (cx(i) >= 0) kn[k] += v;   // the six populations that come from x-1 or x
             }
         }
     }
@@ -706,6 +714,27 @@ __device__ __forceinline__ Node finish(const SlotDesc &S, const Raw18<ST> &raw, 
         rr = red ? rin : 0.f;
         rb = red ? 0.f : rin;
     } else if (xc.outlet) {
+        // the six populations of each colour that come from x-1 or x
+        float kn[2] = {0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            if (cx(i) < 0) continue;
+            float vr, vb;
+            if constexpr (rest32<ST>()) {
+                double e;
+                if (i == 0) {
+                    vr = dec_rest(raw.r0[0], S.rest0[0], e);
+                    vb = dec_rest(raw.r0[1], S.rest0[1], e);
+                } else {
+                    split(nd.n[i], raw.v[9 + i], vr, vb);
+                }
+            } else {
+                vr = C::dec(raw.v[i], S, 0, vclass(i));
+                vb = C::dec(raw.v[9 + i], S, 1, vclass(i));
+            }
+            kn[0] += vr;
+            kn[1] += vb;
+        }
         const float vr = kn[0] * S.inv_rho0[0], vb = kn[1] * S.inv_rho0[1];
         // colour fractions, (phi + 1) / 2 with phi in [-1, 1]: clamped, so that
         // a trace colour whose incoming populations sum below zero (16-bit
@@ -736,28 +765,6 @@ __device__ __forceinline__ Node finish(const SlotDesc &S, const Raw18<ST> &raw, 
     return nd;
 }
 
-// Exact colour-mass bookkeeping of the FP32 path: the rounding of the 18
-// outputs of a node (of the order of an ulp of the rest population, and the
-// same at every node of a uniform region) is measured in FP64 and returned to
-// the four diagonal populations of each colour, whose ulp is 16-32 times
-// finer.  Per step, each node then conserves the mass of each colour to a few
-// ulps of its smallest populations.
-__device__ __forceinline__ void conserve(const Node &nd, float *outr, float *outb)
-{
-    double sr = 0.0, sb = 0.0;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) {
-        sr += (double)outr[i];
-        sb += (double)outb[i];
-    }
-    const float qr = (float)((nd.mr - sr) * 0.25), qb = (float)((nd.mb - sb) * 0.25);
-#pragma unroll
-    for (int i = 5; i < 9; ++i) {
-        outr[i] += qr;
-        outb[i] += qb;
-    }
-}
-
 // Where one node's populations sit: its column in a run of stored values
 // (col_off), its FP32 rest population (rest_col_off, 16-bit storage) and its
 // row (row_bytes multiple); pos = 2 (y pitch + x), the node's position for the
@@ -770,6 +777,15 @@ __device__ __forceinline__ NodeAt node_at(const SlotDesc &S, int x, int y)
 {
     return NodeAt{col_off<ST>(x), rest_col_off<ST>(x), (uint32_t)y * (uint32_t)S.row_bytes,
                   2u * ((uint32_t)y * (uint32_t)S.pitch + (uint32_t)x)};
+}
+
+// The two rest populations of a node in 16-bit storage.
+__device__ __forceinline__ void store_rest(const SlotDesc &S, const Halves &h, const NodeAt &at, double r, double b,
+                                           uint32_t seed)
+{
+    const uint32_t r1 = CG_CODEC_SR ? weyl(seed, 9) : kRestHalf, r2 = CG_CODEC_SR ? weyl(seed, 10) : kRestHalf;
+    __builtin_amdgcn_raw_buffer_store_b32(enc_rest(r, S.rest0[0], r1), h.r[0], (int)at.rcol, (int)at.row, CG_STORE_POLICY);
+    __builtin_amdgcn_raw_buffer_store_b32(enc_rest(b, S.rest0[1], r2), h.r[1], (int)at.rcol, (int)at.row, CG_STORE_POLICY);
 }
 
 // Store the 18 post-recolouring populations of one node; mr, mb: the colour
@@ -793,24 +809,19 @@ __device__ __forceinline__ void store18(const SlotDesc &S, const Halves &h, cons
         // one seed per node from its position and two of the values stored
         const uint32_t seed = mix32(at.pos ^ __float_as_uint(outr[1]) ^
                                     __builtin_rotateleft32(__float_as_uint(outb[5]), 13));
-        double ar = 0.0, ab = 0.0;
+        double sn = 0.0, sr = 0.0;
 #pragma unroll
         for (int i = 1; i < 9; ++i) {
             uint16_t q, u;
-            float nr, nb;
-            enc_pair<ST>(S, vclass(i), outr[i], outb[i], weyl(seed, 2 * i), weyl(seed, 2 * i + 1), CG_CODEC_SR != 0,
-                         q, u, nr, nb);
-            ar += (double)nr;
-            ab += (double)nb;
+            float N, nr;
+            enc_pair<ST>(S, vclass(i), outr[i] + outb[i], pair_share(outr[i], outb[i]), weyl(seed, i), CG_CODEC_SR != 0, q, u,
+                         N, nr);
+            sn += (double)N;
+            sr += (double)nr;
             C::put(q, h.r[0], at.col, plane_off<ST>(i) + at.row);
             C::put(u, h.r[1], at.col, plane_off<ST>(i) + at.row);
         }
-        const uint32_t r1 = weyl(seed, 18), r2 = weyl(seed, 19);
-        const double d1 = CG_CODEC_SR ? (double)(r1 >> 8) * 0x1p-24 : 0.5, d2 = CG_CODEC_SR ? (double)(r2 >> 8) * 0x1p-24 : 0.5;
-        __builtin_amdgcn_raw_buffer_store_b32(enc_rest(mr - ar, S.rest0[0], d1), h.r[0], (int)at.rcol, (int)at.row,
-                                              CG_STORE_POLICY);
-        __builtin_amdgcn_raw_buffer_store_b32(enc_rest(mb - ab, S.rest0[1], d2), h.r[1], (int)at.rcol, (int)at.row,
-                                              CG_STORE_POLICY);
+        store_rest(S, h, at, mr - sr, mb - (sn - sr), seed);
     }
 }
 
@@ -831,14 +842,14 @@ __device__ __forceinline__ void store18_nearest(const SlotDesc &S, const Halves 
 #pragma unroll
         for (int i = 1; i < 9; ++i) {
             uint16_t q, u;
-            float nr, nb;
-            enc_pair<ST>(S, vclass(i), outr[i], outb[i], 0u, 0u, false, q, u, nr, nb);
+            float N, nr;
+            enc_pair<ST>(S, vclass(i), outr[i] + outb[i], pair_share(outr[i], outb[i]), 0u, false, q, u, N, nr);
             C::put(q, h.r[0], at.col, plane_off<ST>(i) + at.row);
             C::put(u, h.r[1], at.col, plane_off<ST>(i) + at.row);
         }
-        __builtin_amdgcn_raw_buffer_store_b32(enc_rest((double)outr[0], S.rest0[0], 0.5), h.r[0], (int)at.rcol,
+        __builtin_amdgcn_raw_buffer_store_b32(enc_rest((double)outr[0], S.rest0[0], kRestHalf), h.r[0], (int)at.rcol,
                                               (int)at.row, CG_STORE_POLICY);
-        __builtin_amdgcn_raw_buffer_store_b32(enc_rest((double)outb[0], S.rest0[1], 0.5), h.r[1], (int)at.rcol,
+        __builtin_amdgcn_raw_buffer_store_b32(enc_rest((double)outb[0], S.rest0[1], kRestHalf), h.r[1], (int)at.rcol,
                                               (int)at.row, CG_STORE_POLICY);
     }
 }
@@ -886,21 +897,26 @@ __device__ __forceinline__ float color_field(const SlotDesc &S, float rr, float 
     return b == 0.f ? 1.f : (a == 0.f ? -1.f : psi);   // exactly +-1 in a pure fluid
 }
 
-// Velocity with the half-force shift of Guo forcing.
-__device__ __forceinline__ void velocity(const SlotDesc &S, const Node &nd, float rho, float &ux, float &uy)
+// Momentum with the half-force shift of Guo forcing.
+__device__ __forceinline__ void momentum(const SlotDesc &S, const Node &nd, float rho, float &jx, float &jy)
 {
 #pragma clang fp contract(off)   // the same for a node's owner and a halo lane (Q of the correction)
     const float *N = nd.n;
-    const float jx = (N[1] - N[3]) + (N[5] - N[7]) + (N[8] - N[6]);
-    const float jy = (N[2] - N[4]) + (N[5] - N[7]) + (N[6] - N[8]);
-    const float ir = fast_rcp(rho);
+    jx = (N[1] - N[3]) + (N[5] - N[7]) + (N[8] - N[6]);
+    jy = (N[2] - N[4]) + (N[5] - N[7]) + (N[6] - N[8]);
     if (S.flags & F_FORCE) {
-        ux = (jx + 0.5f * rho * S.gx) * ir;
-        uy = (jy + 0.5f * rho * S.gy) * ir;
-    } else {
-        ux = jx * ir;
-        uy = jy * ir;
+        jx = jx + 0.5f * rho * S.gx;
+        jy = jy + 0.5f * rho * S.gy;
     }
+}
+// The velocity of it.
+__device__ __forceinline__ void velocity(const SlotDesc &S, const Node &nd, float rho, float &ux, float &uy)
+{
+#pragma clang fp contract(off)
+    momentum(S, nd, rho, ux, uy);
+    const float ir = fast_rcp(rho);
+    ux = ux * ir;
+    uy = uy * ir;
 }
 
 // omega_eff, quadratic interpolation across the interface (Sec. 2.1.1).
@@ -910,45 +926,6 @@ __device__ __forceinline__ float omega_eff(const SlotDesc &S, float psi)
     if (psi > 0.f) return S.chi + psi * (S.eta + S.kappa * psi);
     if (psi >= -S.delta) return S.chi + psi * (S.lam + S.nu * psi);
     return S.omega_b;
-}
-
-// M x for the D2Q9 moment basis of Appendix B (rows: rho, e, eps, jx, qx,
-// jy, qy, pxx, pxy).
-__device__ __forceinline__ void mrt_fwd(const float *f, float *m)
-{
-    const float a = f[1] + f[2] + f[3] + f[4];
-    const float d = f[5] + f[6] + f[7] + f[8];
-    m[0] = f[0] + a + d;
-    m[1] = -4.f * f[0] - a + 2.f * d;
-    m[2] = 4.f * f[0] - 2.f * a + d;
-    const float dx = f[5] - f[6] - f[7] + f[8];
-    const float dy = f[5] + f[6] - f[7] - f[8];
-    m[3] = (f[1] - f[3]) + dx;
-    m[4] = -2.f * (f[1] - f[3]) + dx;
-    m[5] = (f[2] - f[4]) + dy;
-    m[6] = -2.f * (f[2] - f[4]) + dy;
-    m[7] = (f[1] + f[3]) - (f[2] + f[4]);
-    m[8] = (f[5] + f[7]) - (f[6] + f[8]);
-}
-
-// M^{-1} m = M^T diag(1/9, 1/36, 1/36, 1/6, 1/12, 1/6, 1/12, 1/4, 1/4) m
-__device__ __forceinline__ void mrt_inv(const float *m, float *f)
-{
-    const float a0 = m[0] * (1.f / 9.f), a1 = m[1] * (1.f / 36.f), a2 = m[2] * (1.f / 36.f);
-    const float a3 = m[3] * (1.f / 6.f), a4 = m[4] * (1.f / 12.f), a5 = m[5] * (1.f / 6.f);
-    const float a6 = m[6] * (1.f / 12.f), a7 = m[7] * 0.25f, a8 = m[8] * 0.25f;
-    f[0] = a0 - 4.f * a1 + 4.f * a2;
-    const float ax = a0 - a1 - 2.f * a2;
-    f[1] = ax + a3 - 2.f * a4 + a7;
-    f[3] = ax - a3 + 2.f * a4 + a7;
-    f[2] = ax + a5 - 2.f * a6 - a7;
-    f[4] = ax - a5 + 2.f * a6 - a7;
-    const float dg = a0 + 2.f * a1 + a2;
-    const float px = a3 + a4, py = a5 + a6;
-    f[5] = dg + px + py + a8;
-    f[6] = dg - px + py - a8;
-    f[7] = dg - px - py + a8;
-    f[8] = dg + px - py - a8;
 }
 
 // Wetting (Sec. 2.4) at a node of the first (bottom) or last row next to a
@@ -971,180 +948,273 @@ __device__ __forceinline__ void wet(const SlotDesc &S, bool bottom, float &Fx, f
     Fy = Fm * (bottom ? ty : -ty);
 }
 
+// A node after collision and perturbation, before the recolouring split.
+struct Post {
+    float n[9];             // colour-blind populations N**
+    float cmin;             // fraction of the minority colour (exactly 0 for an absent one)
+    bool red_minor;
+    float gx, gy, gp, gm;   // segregation term of directions 1, 2, 5 and 8 (the opposite ones: negated),
+                            // added to the minority colour and taken from the majority one
+    __device__ __forceinline__ float seg(int i) const
+    {
+        return i == 1 ? gx : i == 3 ? -gx : i == 2 ? gy : i == 4 ? -gy : i == 5 ? gp : i == 7 ? -gp : i == 8 ? gm
+             : i == 6 ? -gm : 0.f;
+    }
+};
+
 // Collision (Sec. 2.1.1 BGK / Sec. 2.1.2 MRT, colour-blind), perturbation
-// (Sec. 2.2) and recolouring (Sec. 2.3) of one node.  F = colour gradient,
-// psi = own colour field.  Output: red and blue post-recolouring populations.
+// (Sec. 2.2) and the recolouring's coefficients (Sec. 2.3) of one node.
+// F = colour gradient, psi = own colour field.
 // NSC (compiled in) with nsc (the lattice's flag): the Navier-Stokes
 // correction of Sec. 2.1.3, i.e. the Hermite equilibrium and the MRT source
 // M^-1 C from dqx = dQx/dx, dqy = dQy/dy of Q = sum_k (1.8 alpha_k - 0.8) rho_k u.
-// Each output pair goes to sink(i, red, blue) as soon as it is formed (in
-// the order i = 0 .. 8), so that a sink that stores can let it go at once.
-template <bool NSC = false, class Sink>
-__device__ __forceinline__ void collide(const SlotDesc &S, const Node &nd, float psi, float Fx, float Fy, Sink &&sink,
+//
+// Every term but the populations themselves is the same for the two opposite
+// directions of a pair (even) or changes sign (odd), so each is formed once
+// per pair: equilibrium e_i = s_pair +- l_pair, forcing, source and
+// perturbation in `ev` (even) and in l (odd).  MRT: rates s_0..s_6 are all
+// lambda w and s_7 = s_8 = w, so N - M^-1 S M (N - N^e) is BGK with the rate
+// lambda w plus the part (w - lambda w) of the two stress moments m_7, m_8,
+// whose columns of M^-1 are +-1/4 on the axis and on the diagonal directions.
+// (Written direction by direction, with products by the zero components of
+// c_i left to a compiler that must keep them and with the full 9 x 9 moment
+// transforms, the step spent 8.4 VALU instructions per update where this
+// form takes about 5.)
+//
+// No contraction: every kernel variant must round this alike, so the fused
+// multiply-adds are spelled out.
+template <bool NSC = false>
+__device__ __forceinline__ Post collide(const SlotDesc &S, const Node &nd, float psi, float Fx, float Fy,
                                         bool nsc = false, float dqx = 0.f, float dqy = 0.f)
 {
+#pragma clang fp contract(off)
+    const auto fma = [](float a, float b, float c) { return __builtin_fmaf(a, b, c); };
     const float rr = nd.rr(), rb = nd.rb();
     const float rho = rr + rb;
-    float ux, uy;
-    velocity(S, nd, rho, ux, uy);
+    float jx, jy;
+    momentum(S, nd, rho, jx, jy);
+    const float irho = refined_rcp(rho);
+    const float ux = jx * irho, uy = jy * irho;
     const float w = omega_eff(S, psi);
-    const float uu = ux * ux + uy * uy;
+    const bool mrt = S.flags & F_MRT;
+    const float rate = mrt ? S.mrt_lambda * w : w;
 
-    float neq[9];     // N - N^(e)
-    const bool force = S.flags & F_FORCE;
-    const float gxr = rho * S.gx, gyr = rho * S.gy;
-    // Guo forcing source of direction i (force density rho g); evaluated only
-    // under the uniform branch of a forced lattice
-    auto guo = [&](int i) {
-        const float cu = cx(i) * ux + cy(i) * uy;
-        return wgt(i) * ((3.f * (cx(i) - ux) + 9.f * cu * cx(i)) * gxr + (3.f * (cy(i) - uy) + 9.f * cu * cy(i)) * gyr);
-    };
-    // Hermite equilibrium: the linear term of colour k carries the factor
-    // 1 + (3 c_s,k^2 - 1)(3 |c_i|^2 - 4) / 2; summed over the colours its
-    // density is rho + hco(i) K with K = sum_k rho_k (3 c_s,k^2 - 1)
-    const bool herm = NSC && nsc;
-    const float K = herm ? rr * S.k3[0] + rb * S.k3[1] : 0.f;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) {
-        const float cu = cx(i) * ux + cy(i) * uy;
-        const int c = vclass(i);
-        // N - N^(e) with the rest part subtracted by fused multiply-adds: the
-        // large rest populations of a heavy fluid never get rounded on their own
-        float t = __builtin_fmaf(-rr, S.phi[0][c], nd.n[i]);
-        t = __builtin_fmaf(-rb, S.phi[1][c], t);
-        // unit mass of the FP32 rest weights, and the exact mass of the node
-        if (i == 0) t -= rr * S.phi0_eps[0] + rb * S.phi0_eps[1] + nd.dm();
-        if (herm && i != 0)
-            neq[i] = t - wgt(i) * (3.f * cu * __builtin_fmaf(hco(i), K, rho) + rho * (4.5f * cu * cu - 1.5f * uu));
-        else
-            neq[i] = t - rho * wgt(i) * (3.f * cu + 4.5f * cu * cu - 1.5f * uu);
-    }
-    float ns[9];
-    if (S.flags & F_MRT) {
-        float m[9], q[9];
-        mrt_fwd(neq, m);
-        const float sl = S.mrt_lambda * w;
-        if (force) {
-            float G[9], mg[9];
-#pragma unroll
-            for (int i = 0; i < 9; ++i) G[i] = guo(i);
-            mrt_fwd(G, mg);
-#pragma unroll
-            for (int j = 0; j < 9; ++j) {
-                const float s = (j >= 7) ? w : sl;
-                q[j] = s * m[j] - (1.f - 0.5f * s) * mg[j];
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < 9; ++j) q[j] = ((j >= 7) ? w : sl) * m[j];
-        }
-        if (herm) {
-            // source U = M^-1 C, C_1 = 3 (1 - s_1/2)(dQx/dx + dQy/dy),
-            // C_7 = (1 - s_7/2)(dQx/dx - dQy/dy): N* = N - M^-1 (q - C)
-            q[1] -= 3.f * (1.f - 0.5f * sl) * (dqx + dqy);
-            q[7] -= (1.f - 0.5f * w) * (dqx - dqy);
-        }
-        float dn[9];
-        mrt_inv(q, dn);
-#pragma unroll
-        for (int i = 0; i < 9; ++i) ns[i] = nd.n[i] - dn[i];
-    } else {
-        if (force) {
-            const float hf = 1.f - 0.5f * w;
-#pragma unroll
-            for (int i = 0; i < 9; ++i) ns[i] = __builtin_fmaf(hf, guo(i), __builtin_fmaf(-w, neq[i], nd.n[i]));
-        } else {
-#pragma unroll
-            for (int i = 0; i < 9; ++i) ns[i] = __builtin_fmaf(-w, neq[i], nd.n[i]);
-        }
+    // equilibrium without its rest part: second-order terms per pair (x, y,
+    // p = the 5-7 and m = the 8-6 diagonal) and linear terms of 1, 2, 5, 8
+    const float up = ux + uy, um = ux - uy;
+    const float u6 = fma(ux, ux, uy * uy) * (1.f / 6.f);      // u^2 / 6
+    const float sx = rho * fma(0.5f * ux, ux, -u6), sy = rho * fma(0.5f * uy, uy, -u6);
+    const float sp = rho * fma(0.125f * up, up, -0.25f * u6), sm = rho * fma(0.125f * um, um, -0.25f * u6);
+    // the linear terms carry the node's momentum as it is, with weights that
+    // sum to exactly 1 (1/3 and 1/12 both round up): relative errors of 3e-8 in
+    // it would accumulate coherently over the steps of a steady flow
+    constexpr float ka = 1.f / 3.f, kd = 0.25f - 0.5f * ka;
+    const float jp = jx + jy, jm = jx - jy;
+    float lx = ka * jx, ly = ka * jy, lp = kd * jp, lm = kd * jm;
+    if (NSC && nsc) {
+        // Hermite equilibrium: the linear term of colour k carries the factor
+        // 1 + (3 c_s,k^2 - 1)(3 |c_i|^2 - 4) / 2, i.e. summed over the colours
+        // -K/2 on the axis and K on the diagonal directions with
+        // K = sum_k rho_k (3 c_s,k^2 - 1); weights without net momentum
+        constexpr float kk = 1.f / 12.f;
+        const float K = fma(rr, S.k3[0], rb * S.k3[1]);
+        lx = fma(-2.f * kk, K * ux, lx);
+        ly = fma(-2.f * kk, K * uy, ly);
+        lp = fma(kk, K * up, lp);
+        lm = fma(kk, K * um, lm);
     }
 
-    const float F2 = Fx * Fx + Fy * Fy;
+    // even terms added to the relaxed populations: perturbation (below),
+    // forcing, source of the correction
+    float ex = 0.f, ey = 0.f, ep = 0.f, em = 0.f, e0 = 0.f;
+    float g7 = 0.f, g8 = 0.f;                                 // half the forcing's m_7 and m_8
+    if (S.flags & F_FORCE) {
+        // Guo forcing (force density rho g): W_i [3 (c_i - u) + 9 (c_i.u) c_i].rho g,
+        // relaxed with 1 - s/2; the odd part 3 W_i c_i.rho g joins the linear terms
+        const float fx = rho * S.gx, fy = rho * S.gy, fp = fx + fy, fm = fx - fy;
+        const float ug = fma(ux, fx, uy * fy) * (1.f / 3.f);
+        const float hf = fma(-0.5f, rate, 1.f);
+        const float ho = hf * refined_rcp(rate);
+        const float vx = fma(ux, fx, -ug), vy = fma(uy, fy, -ug);
+        const float vp = 0.25f * (fma(up, fp, -ug)), vm = 0.25f * (fma(um, fm, -ug));
+        lx = fma(ho * ka, fx, lx);
+        ly = fma(ho * ka, fy, ly);
+        lp = fma(ho * kd, fp, lp);
+        lm = fma(ho * kd, fm, lm);
+        ex = hf * vx;
+        ey = hf * vy;
+        ep = hf * vp;
+        em = hf * vm;
+        e0 = hf * (-4.f * ug);
+        g7 = vx - vy;
+        g8 = vp - vm;
+    }
+
+    // No gradient (|F| <= 1e-12): neither perturbation nor segregation.  Away
+    // from interfaces that holds for a whole wavefront, which then skips both.
+    const float F2 = fma(Fx, Fx, Fy * Fy);
+    const bool pert = F2 > 1e-24f;
+    Post P;
     // Recolouring split: the minority colour is computed from its own fraction
     // (keeping its relative precision in the tails of an interface) and the
     // majority colour as the difference, so that N^r + N^b = N** holds to the
     // last bit and the colour-blind mass is untouched by the split.
-    const float irho = refined_rcp(rho);
-    const bool red_minor = rr < rb;
-    const float cmin = (red_minor ? rr : rb) * irho;    // 0 exactly for an absent colour
-    const float cmaj = (red_minor ? rb : rr) * irho;
-    const float sgn = red_minor ? 1.f : -1.f;           // the segregation term adds to red
-    // no gradient (|F| <= 1e-12): neither perturbation nor segregation.  Both
-    // forms are evaluated and selected per lane (uniform control flow, so that
-    // every store of a row is one instruction over the whole wavefront).
-    const bool pert = F2 > 1e-24f;
-    const float inv = pert ? __builtin_amdgcn_rsqf(F2) : 0.f;   // 1/|F|
-    const float Fm = F2 * inv;                                   // |F|
-    const float A = (S.flags & F_SIGMA) ? S.sigma94 * w : S.A;
-    const float seg = S.beta * cmin * cmaj;
+    P.red_minor = rr < rb;
+    P.cmin = (P.red_minor ? rr : rb) * irho;
+    P.gx = P.gy = P.gp = P.gm = 0.f;
+    if (pert) {
+        const float inv = __builtin_amdgcn_rsqf(F2);
+        const float nx = Fx * inv, ny = Fy * inv, np = nx + ny, nm = nx - ny;   // n = F / |F|
+        const float h = ((S.flags & F_SIGMA) ? S.sigma94 * w : S.A) * (F2 * inv);   // A |F|
+        const float ha = h * wgt(1), hd = h * wgt(5);
+        ex += fma(ha * nx, nx, -bco(1) * h);
+        ey += fma(ha * ny, ny, -bco(1) * h);
+        ep += fma(hd * np, np, -bco(5) * h);
+        em += fma(hd * nm, nm, -bco(5) * h);
+        e0 += -bco(0) * h;
+        // beta c_r c_b cos(phi_i) sum_k rho_k phi^k_i; phi^k of a diagonal
+        // direction is a quarter of an axis one's, and |c_i| = sqrt(2)
+        const float cmaj = (P.red_minor ? rb : rr) * irho;
+        const float seg = S.beta * P.cmin * cmaj * fma(rr, S.phi[0][1], rb * S.phi[1][1]);
+        const float sg = P.red_minor ? seg : -seg;          // it adds to red
+        P.gx = sg * nx;
+        P.gy = sg * ny;
+        P.gp = 0.17677669529663687f * (sg * np);
+        P.gm = 0.17677669529663687f * (sg * nm);
+    }
+
+    // y_i = N_i - N^e_i with the rest part subtracted by fused multiply-adds:
+    // the large rest populations of a heavy fluid never get rounded on their own
+    const auto rest = [&](int i) { return fma(-rb, S.phi[1][vclass(i)], fma(-rr, S.phi[0][vclass(i)], nd.n[i])); };
+    float y[9];
+    // unit mass of the FP32 rest weights, and the exact mass of the node
+    y[0] = fma(4.f * rho, u6, rest(0) - (fma(rr, S.phi0_eps[0], rb * S.phi0_eps[1]) + nd.dm()));
+    y[1] = rest(1) - (sx + lx);
+    y[3] = rest(3) - (sx - lx);
+    y[2] = rest(2) - (sy + ly);
+    y[4] = rest(4) - (sy - ly);
+    y[5] = rest(5) - (sp + lp);
+    y[7] = rest(7) - (sp - lp);
+    y[8] = rest(8) - (sm + lm);
+    y[6] = rest(6) - (sm - lm);
+    if (mrt) {
+        const float k = 0.25f * (w - rate);
+        float z7 = k * (((y[1] + y[3]) - (y[2] + y[4])) + g7), z8 = k * (((y[5] + y[7]) - (y[6] + y[8])) + g8);
+        if (NSC && nsc) {
+            // source M^-1 C, C_1 = 3 (1 - s_1/2)(dQx/dx + dQy/dy),
+            // C_7 = (1 - s_7/2)(dQx/dx - dQy/dy)
+            const float c1 = fma(-0.5f, rate, 1.f) * (dqx + dqy) * (1.f / 12.f);
+            z7 = fma(-0.25f * fma(-0.5f, w, 1.f), dqx - dqy, z7);
+            e0 -= 4.f * c1;
+            ex -= c1;
+            ey -= c1;
+            ep = fma(2.f, c1, ep);
+            em = fma(2.f, c1, em);
+        }
+        ex -= z7;
+        ey += z7;
+        ep -= z8;
+        em += z8;
+    }
+    // the change of each population is formed whole and subtracted once: one
+    // rounding at the size of the population itself
+    P.n[0] = nd.n[0] - fma(rate, y[0], -e0);
+    P.n[1] = nd.n[1] - fma(rate, y[1], -ex);
+    P.n[2] = nd.n[2] - fma(rate, y[2], -ey);
+    P.n[3] = nd.n[3] - fma(rate, y[3], -ex);
+    P.n[4] = nd.n[4] - fma(rate, y[4], -ey);
+    P.n[5] = nd.n[5] - fma(rate, y[5], -ep);
+    P.n[6] = nd.n[6] - fma(rate, y[6], -em);
+    P.n[7] = nd.n[7] - fma(rate, y[7], -ep);
+    P.n[8] = nd.n[8] - fma(rate, y[8], -em);
+    return P;
+}
+
+// The recolouring split of direction i (Sec. 2.3): red and blue populations.
+__device__ __forceinline__ void recolor(const Post &P, int i, float &r, float &b)
+{
+#pragma clang fp contract(off)
+    const float mino = i == 0 ? P.cmin * P.n[0] : __builtin_fmaf(P.cmin, P.n[i], P.seg(i));
+    const float majo = P.n[i] - mino;
+    r = P.red_minor ? mino : majo;
+    b = P.red_minor ? majo : mino;
+}
+
+// FP32 storage: split and store one node.  The rounding of the 18 outputs (of
+// the order of an ulp of the rest population, and the same at every node of a
+// uniform region) is measured in FP64 and returned to the four diagonal
+// populations of each colour, whose ulp is 16-32 times finer: per step, each
+// node conserves the mass of each colour to a few ulps of its smallest
+// populations.  POL: cache policy bits of the stores.
+template <int POL = CG_STORE_POLICY>
+__device__ __forceinline__ void store_f32_node(const Halves &h, const NodeAt &at, const Post &P, double mr, double mb)
+{
+    const auto put = [&](int i, int k, float v) {
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), h.r[k], (int)at.col,
+                                              (int)(plane_off<ST_F32>(i) + at.row), POL);
+    };
+    float kr[4], kb[4];
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
-        const float fc = cx(i) * Fx + cy(i) * Fy;
-        const float nss = ns[i] + A * (wgt(i) * fc * fc * inv - bco(i) * Fm);
-        float sg = 0.f;
-        if (i != 0) {
-            const int c = vclass(i);
-            const float cosphi = fc * inv * (c == 1 ? 1.f : 0.70710678118654752f);
-            sg = seg * cosphi * (rr * S.phi[0][c] + rb * S.phi[1][c]);
+        float r, b;
+        recolor(P, i, r, b);
+        mr -= (double)r;
+        mb -= (double)b;
+        if (i < 5) {
+            put(i, 0, r);
+            put(i, 1, b);
+        } else {
+            kr[i - 5] = r;
+            kb[i - 5] = b;
         }
-        const float mino_p = cmin * nss + sgn * sg;
-        const float majo_p = nss - mino_p;
-        const float mino_0 = cmin * ns[i];
-        const float majo_0 = ns[i] - mino_0;
-        const float mino = pert ? mino_p : mino_0;
-        const float majo = pert ? majo_p : majo_0;
-        sink(i, red_minor ? mino : majo, red_minor ? majo : mino);
+    }
+    const float qr = (float)mr, qb = (float)mb;
+#pragma unroll
+    for (int i = 5; i < 9; ++i) {
+        put(i, 0, __builtin_fmaf(0.25f, qr, kr[i - 5]));
+        put(i, 1, __builtin_fmaf(0.25f, qb, kb[i - 5]));
     }
 }
 
-// A sink that keeps the 18 outputs.
-struct Keep18 {
-    float r[9], b[9];
-    __device__ __forceinline__ void operator()(int i, float vr, float vb)
-    {
-        r[i] = vr;
-        b[i] = vb;
-    }
-};
-
-// FP32 storage: the sink stores each output pair as it comes, keeping only
-// the four diagonal pairs, which take the node's colour-mass residual at the
-// end (the exact bookkeeping of conserve(), in the same order).  POL: cache
-// policy bits of the stores.
-template <int POL = CG_STORE_POLICY>
-struct StoreF32 {
-    const SlotDesc &S;
-    const Halves &h;
-    NodeAt at;
-    double sr, sb;
-    float kr[4], kb[4];
-    static __device__ __forceinline__ void store_f32p(float v, Rsrc r, uint32_t voff, uint32_t soff)
-    {
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, (int)voff, (int)soff, POL);
-    }
-    __device__ __forceinline__ StoreF32(const SlotDesc &s, const Halves &hh, const NodeAt &a)
-        : S(s), h(hh), at(a), sr(0.0), sb(0.0) {}
-    __device__ __forceinline__ void operator()(int i, float vr, float vb)
-    {
-        sr += (double)vr;
-        sb += (double)vb;
-        if (i < 5) {
-            store_f32p(vr, h.r[0], at.col, plane_off<ST_F32>(i) + at.row);
-            store_f32p(vb, h.r[1], at.col, plane_off<ST_F32>(i) + at.row);
-        } else {
-            kr[i - 5] = vr;
-            kb[i - 5] = vb;
-        }
-    }
-    __device__ __forceinline__ void finish(const Node &nd)
-    {
-        const float qr = (float)((nd.mr - sr) * 0.25), qb = (float)((nd.mb - sb) * 0.25);
+// 16-bit storage: encode and store one node.  The share of direction i is
+// the red fraction of the node plus its segregation term over N**_i; where no
+// lane of a wavefront has one, every direction has the same share.
+template <int ST>
+__device__ __forceinline__ void store_16_node(const SlotDesc &S, const Halves &h, const NodeAt &at, const Post &P,
+                                              double mr, double mb)
+{
+#pragma clang fp contract(off)
+    using C = Codec<ST>;
+    const float c1 = (P.red_minor ? P.cmin : 1.f - P.cmin) * kShareOne;   // exactly 0 / kShareOne for an absent colour
+    uint32_t t[9];
+    const uint32_t t0 = fix_share(c1);
 #pragma unroll
-        for (int i = 5; i < 9; ++i) {
-            store_f32p(kr[i - 5] + qr, h.r[0], at.col, plane_off<ST_F32>(i) + at.row);
-            store_f32p(kb[i - 5] + qb, h.r[1], at.col, plane_off<ST_F32>(i) + at.row);
-        }
+    for (int i = 1; i < 9; ++i) t[i] = t0;
+    if (P.gx != 0.f || P.gy != 0.f) {
+        const float k = P.red_minor ? kShareOne : -kShareOne;
+#pragma unroll
+        for (int i = 1; i < 9; ++i) t[i] = fix_share(__builtin_fmaf(P.seg(i) * k, __builtin_amdgcn_rcpf(P.n[i]), c1));
     }
-};
+    // One seed per node from its position, one of the values stored and its
+    // exact colour masses, whose last bits carry the previous step's share
+    // dither: a steady node then draws anew every step (seeded by N** alone,
+    // which there takes a few values only, it repeated its rounding errors and
+    // the 64 x 64 bubble's colour mass drifted by 4e-7 in 20000 steps).
+    const uint64_t br = (uint64_t)__double_as_longlong(mr), bb = (uint64_t)__double_as_longlong(mb);
+    const uint32_t seed = mix32(at.pos ^ __float_as_uint(P.n[1]) ^ (uint32_t)(br >> 16) ^
+                                __builtin_rotateleft32((uint32_t)(bb >> 16), 13));
+    double sn = 0.0, sr = 0.0;
+#pragma unroll
+    for (int i = 1; i < 9; ++i) {
+        uint16_t q, u;
+        float N, nr;
+        enc_pair<ST>(S, vclass(i), P.n[i], t[i], weyl(seed, i), CG_CODEC_SR != 0, q, u, N, nr);
+        sn = i == 1 ? (double)N : sn + (double)N;
+        sr = i == 1 ? (double)nr : sr + (double)nr;
+        C::put(q, h.r[0], at.col, plane_off<ST>(i) + at.row);
+        C::put(u, h.r[1], at.col, plane_off<ST>(i) + at.row);
+    }
+    store_rest(S, h, at, mr - sr, mb - (sn - sr), seed);
+}
 
 }  // namespace cgd

@@ -47,50 +47,56 @@ __device__ __forceinline__ int find_slot(const SlotDesc *__restrict__ slots, int
 // lane l-1 (west) and of lane l+1 (east).
 __device__ __forceinline__ float from_west(float v)
 {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, false));
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x138, 0xf, 0xf, true));
 }
 __device__ __forceinline__ float from_east(float v)
 {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, false));
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x130, 0xf, 0xf, true));
 }
 
-// Colour field of one row with its west and east neighbours.
+// Colour field of one row: its value, and the difference and sum of its east
+// and west neighbours, the form in which all three rows of a stencil use it.
 struct Psi3 {
-    float w, c, e;
+    float c, d, s;
 };
 
-__device__ __forceinline__ Psi3 psi3(float c) { return Psi3{from_west(c), c, from_east(c)}; }
+__device__ __forceinline__ Psi3 psi3(float c)
+{
+    const float w = from_west(c), e = from_east(c);
+    return Psi3{c, e - w, e + w};
+}
+
+// S2I4 gradient, Sec. 2.2 eq. (colorGradient): xi = 1/3 axis, 1/12 diagonal,
+// from the rows behind, at and ahead of the node; fd = +1 / -1 when marching
+// up / down.  The two outer rows enter by their sum and difference only, so
+// the result does not depend on the direction; no contraction, so that every
+// kernel variant rounds it alike.
+template <class Row>
+__device__ __forceinline__ void gradient(const Row &pb, const Row &p0, const Row &pa, float fd, float &Fx, float &Fy)
+{
+#pragma clang fp contract(off)
+    Fx = __builtin_fmaf(1.f / 3.f, p0.d, (1.f / 12.f) * (pa.d + pb.d));
+    Fy = fd * __builtin_fmaf(1.f / 3.f, pa.c - pb.c, (1.f / 12.f) * (pa.s - pb.s));
+}
 
 // Wave tile: 64 lanes cover columns xw-h .. xw+63-h and write the middle
 // 64-2h (h = wave_halo: 2, or 3 with the second-neighbour gradient).
 
 // Collision, perturbation and recolouring of one node and the store of its
-// 18 populations.  FP32: each pair is stored as soon as it is formed, the
-// diagonal ones after the exact colour-mass bookkeeping; 16-bit storage
-// (which rounds far coarser and keeps colour mass in its codec) encodes the
-// 18 outputs together.
-// POL: cache policy of the FP32 stores.
+// 18 populations.  POL: cache policy of the FP32 stores.
 template <int ST, bool NSC, int POL = CG_STORE_POLICY>
 __device__ __forceinline__ void collide_store(const SlotDesc &S, const Halves &dst, const NodeAt &at, const Node &cur,
                                               float psi, float Fx, float Fy, bool nsc, float dqx, float dqy)
 {
-    if constexpr (ST == ST_F32) {
-        StoreF32<POL> sk(S, dst, at);
-        if constexpr (NSC) collide<true>(S, cur, psi, Fx, Fy, sk, nsc, dqx, dqy);
-        else collide(S, cur, psi, Fx, Fy, sk);
-        sk.finish(cur);
-    } else {
-        Keep18 k;
-        if constexpr (NSC) collide<true>(S, cur, psi, Fx, Fy, k, nsc, dqx, dqy);
-        else collide(S, cur, psi, Fx, Fy, k);
-        store18<ST>(S, dst, at, k.r, k.b, cur.mr, cur.mb);
-    }
+    const Post P = collide<NSC>(S, cur, psi, Fx, Fy, nsc, dqx, dqy);
+    if constexpr (ST == ST_F32) store_f32_node<POL>(dst, at, P, cur.mr, cur.mb);
+    else store_16_node<ST>(S, dst, at, P, cur.mr, cur.mb);
 }
 
-// Colour field of one row: the lane's own value, its west and east
-// neighbours, and the halo nodes' values (lanes 0, 1, 62, 63; see halo_node).
+// Colour field of one row as Psi3, and the halo nodes' values (lanes 0, 1,
+// 62, 63; see halo_node).
 struct PRow {
-    float w, c, e, h;
+    float c, d, s, h;
 };
 
 // West / east neighbour of each lane's value by a DPP wave shift; lane 0
@@ -216,11 +222,14 @@ __device__ __forceinline__ void step_nn(const SlotDesc *__restrict__ slots, int 
         const float hginv = hgden > 0.f ? fast_rcp(hgden) : 0.f;
         gh = ((hin0 ? 4.f * h : 0.f) + (hinw ? hw : 0.f) + (hine ? he : 0.f)) * hginv;
     };
-    auto prow = [&](float c, float h) { return PRow{west_of(c, h), c, east_of(c, h), h}; };
+    auto prow = [&](float c, float h) {
+        const float w = west_of(c, h), e = east_of(c, h);
+        return PRow{c, e - w, e + w, h};
+    };
     auto ghost = [&](const PRow &f) -> PRow {
         float g, gh;
         ghost_vals(f.c, f.h, g, gh);
-        return PRow{west_of(g, gh), g, east_of(g, gh), gh};
+        return prow(g, gh);
     };
     auto real_row = [&](int r) { return yper ? wrap_near(r, ny) : r; };
     auto gathered = [&](int r) { return yper || (r >= 0 && r < ny); };
@@ -406,10 +415,8 @@ __device__ __forceinline__ void step_nn(const SlotDesc *__restrict__ slots, int 
             if (nsc) qa = qghost(cur, q0);
         }
         if (out_lane) {
-            // S2I4 gradient, Sec. 2.2 eq. (colorGradient): xi = 1/3 axis, 1/12 diagonal;
-            // rows y+1 / y-1 are ahead / behind when marching up, the reverse when down
-            float Fx = (1.f / 3.f) * (p0.e - p0.w) + (1.f / 12.f) * ((pa.e - pa.w) + (pb.e - pb.w));
-            float Fy = fd * ((1.f / 3.f) * (pa.c - pb.c) + (1.f / 12.f) * ((pa.e + pa.w) - (pb.e + pb.w)));
+            float Fx, Fy;
+            gradient(pb, p0, pa, fd, Fx, Fy);
             if ((S.flags & F_WET) && (y == 0 || y == ny - 1)) wet(S, y == 0, Fx, Fy);
             const NodeAt at{xc.o0, xc.r0, (uint32_t)y * (uint32_t)S.row_bytes,
                             2u * ((uint32_t)y * (uint32_t)S.pitch + (uint32_t)xg)};
@@ -471,15 +478,20 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
 
     // wall ghost row from the adjacent fluid row (Sec. 2.4 extrapolation):
     // W-weighted mean over the fluid neighbours, axis : diagonal = 4 : 1,
-    // neighbours beyond an open x face excluded
+    // neighbours beyond an open x face excluded (the neighbour values are
+    // fetched by every lane before any lane selects: a cross-lane read under a
+    // lane condition would see the inactive lanes as zero)
     const bool in0 = xper || (xl >= 0 && xl < nx);
     const bool inw = xper || (xl - 1 >= 0 && xl - 1 < nx);
     const bool ine = xper || (xl + 1 >= 0 && xl + 1 < nx);
     const float gden = (in0 ? 4.f : 0.f) + (inw ? 1.f : 0.f) + (ine ? 1.f : 0.f);
     const float ginv = gden > 0.f ? fast_rcp(gden) : 0.f;
+    auto ghost_of = [&](float c) -> float {
+        const float w = from_west(c), e = from_east(c);
+        return ((in0 ? 4.f * c : 0.f) + (inw ? w : 0.f) + (ine ? e : 0.f)) * ginv;
+    };
     auto ghost = [&](const Psi3 &f) -> Psi3 {
-        const float g = ((in0 ? 4.f * f.c : 0.f) + (inw ? f.w : 0.f) + (ine ? f.e : 0.f)) * ginv;
-        return psi3(g);
+        return psi3(ghost_of(f.c));
     };
     auto real_row = [&](int r) { return yper ? wrap_near(r, ny) : r; };
     auto gathered = [&](int r) { return yper || (r >= 0 && r < ny); };
@@ -515,11 +527,7 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
     auto qghost = [&](const Node &adj) -> QRow {
         float qx, qy;
         qnode(adj, qx, qy);
-        // the neighbour values are fetched by every lane before any lane
-        // selects: a cross-lane read under a lane condition would see the
-        // inactive lanes as zero
-        const Psi3 fx = psi3(qx), fy = psi3(qy);
-        return qrow(ghost(fx).c, ghost(fy).c);
+        return qrow(ghost_of(qx), ghost_of(qy));
     };
 
     // Even strips march up, odd strips march down: the two strips on either
@@ -664,7 +672,12 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
         return;
     }
 
-    // prologue: the row behind the first one, and the first one
+    // prologue: the row behind the first one, the first one and the one ahead,
+    // requested together (one wait for memory, not two: a strip of one row is
+    // little more than its waits)
+    bool have_p = gathered(ys + d);
+    RowSrc rwp = make_row<ST>(S, have_p ? real_row(ys + d) : ys, inlet_wave);
+    Raw18<ST> pend;
     Psi3 pb, p0;                               // colour field of rows y-d and y
     QRow qb{}, q0{};                           // Q partial sums of rows y-d and y (NSC)
     Node cur;
@@ -675,6 +688,7 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
         if (have_b) rb = issue<ST>(S, src, xc, rwb);
         const RowSrc rw0 = make_row<ST>(S, ys, inlet_wave);
         const Raw18<ST> r0 = issue<ST>(S, src, xc, rw0);
+        if (have_p) pend = issue<ST>(S, src, xc, rwp);
         if (have_b) {
             const Node t = finish<ST>(S, rb, xc, rwb);
             pb = psi3(color_field(S, t.rr(), t.rb()));
@@ -688,10 +702,6 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
             if (nsc) qb = qghost(cur);
         }
     }
-    bool have_p = gathered(ys + d);
-    RowSrc rwp = make_row<ST>(S, have_p ? real_row(ys + d) : ys, inlet_wave);
-    Raw18<ST> pend;
-    if (have_p) pend = issue<ST>(S, src, xc, rwp);
 
     const float fd = (float)d;
     for (int y = ys; y != ye; y += d) {
@@ -714,10 +724,8 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
             pend = issue<ST>(S, src, xc, rwp);
         }
         if (out_lane) {
-            // S2I4 gradient, Sec. 2.2 eq. (colorGradient): xi = 1/3 axis, 1/12 diagonal;
-            // rows y+1 / y-1 are ahead / behind when marching up, the reverse when down
-            float Fx = (1.f / 3.f) * (p0.e - p0.w) + (1.f / 12.f) * ((pa.e - pa.w) + (pb.e - pb.w));
-            float Fy = fd * ((1.f / 3.f) * (pa.c - pb.c) + (1.f / 12.f) * ((pa.e + pa.w) - (pb.e + pb.w)));
+            float Fx, Fy;
+            gradient(pb, p0, pa, fd, Fx, Fy);
             if ((S.flags & F_WET) && (y == 0 || y == ny - 1)) wet(S, y == 0, Fx, Fy);
             const NodeAt at{xc.o0, xc.r0, (uint32_t)y * (uint32_t)S.row_bytes,
                             2u * ((uint32_t)y * (uint32_t)S.pitch + (uint32_t)xg)};
