@@ -243,12 +243,6 @@ int xch_tx(int nx, int ny, int variant)
     return (variant & cgd::KV_NSC) ? std::min(tx, 512) : tx;
 }
 
-static int wave_tiles(int nx, bool iso, bool xch)
-{
-    const int cols = cgd::wave_cols(iso, xch);
-    return (nx + cols - 1) / cols;
-}
-
 int plan_strip(long long nodes, int ny, int tiles_x, int storage, int req, bool paired, bool xch)
 {
     if (req > 0) return req < ny ? req : ny;
@@ -286,7 +280,51 @@ int plan_strip(long long nodes, int ny, int tiles_x, int storage, int req, bool 
 }
 
 
-void set_geometry(SlotDesc &d, const lbm_params *p, const Layout &L, int tx, int strip, bool xch)
+// Two steps per launch.  The state is read and written once for two steps, at
+// the price of strips that overlap by three rows and wavefronts by 3 columns
+// (5 next to walls) on either side, i.e. of collisions done twice.  It pays
+// once a launch is bound by memory rather than by waits (us per step, one
+// step a launch against two: 700 x 640 16.3 / 17.1, 768^2 19.5 / 17.4,
+// 1024^2 29.2 / 23.1, 4096 x 256 28.2 / 22.6, 2048^2 126 / 84, the 8192 x 512
+// channel 125 / 91, 4096 x 2048 240 / 170, 8192^2 1811 / 1316).  Not built for
+// 16-bit storage, whose step is bound by the codec's arithmetic (channel 104 /
+// 171, 4096 x 2048 209 / 333), the Navier-Stokes correction (its second
+// stencil) and the second-neighbour gradient (twice the reach).
+bool plan_two(long long nodes, int storage, int variant, int ny)
+{
+    return variant == 0 && storage == LBM_STORE_F32 && ny >= 4 && nodes >= 500000LL;
+}
+
+// Four wavefronts side by side, one on lattices narrow enough for the last
+// workgroup's idle wavefronts (which hold LDS) to matter.
+int two_tx(int nx, int req)
+{
+    if (req) return std::min(req, 256);
+    return nx >= 32 * cgd::two_cols(true) ? 256 : 64;
+}
+
+int two_waves(const lbm_params *p) { return (p->nx + cgd::two_cols(true) - 1) / cgd::two_cols(true); }
+
+// A wavefront holds 9 KB of LDS and 128 VGPRs: 4 per SIMD, 4096 on the chip.
+// Strips are as short as lets all wavefronts in flight be resident with a
+// tenth to spare (a second, partly filled round costs 5-20%: 3000 x 150 with
+// 3 rows 16.7 us a step, with 2 rows and 3900 wavefronts 21.1).  Lattices of
+// several rounds run best with 8 rows, whose overlaps the neighbouring strips
+// still find in L2 (8192^2: 1316 us, 16 rows 1341, 32 rows 1428, one round of
+// 293 rows 1528).
+int plan_two_strip(const lbm_params *p, long long nodes, long long wave_rows, int req)
+{
+    if (req > 0) return std::min(req, p->ny);
+    if (nodes > 7500000LL) return std::min(8, p->ny);
+    const long long room = 3686;
+    int s = (int)std::min<long long>(std::max<long long>(1, wave_rows / room), 128);
+    // this lattice's share of the room, in whole strips
+    const long long mine = (long long)two_waves(p) * p->ny;
+    while (s < 128 && s < p->ny && (long long)two_waves(p) * ((p->ny + s - 1) / s) * wave_rows > room * mine) ++s;
+    return std::min(s, p->ny);
+}
+
+void set_geometry(SlotDesc &d, const lbm_params *p, const Layout &L, int tx, int strip, bool xch, bool two)
 {
     d.nx = p->nx;
     d.ny = p->ny;
@@ -296,7 +334,8 @@ void set_geometry(SlotDesc &d, const lbm_params *p, const Layout &L, int tx, int
                                                                       : cgd::blk_bytes<cgd::ST_F16S>()));
     d.strip = strip;
     const int waves = tx / 64;
-    d.tiles_x = (wave_tiles(p->nx, p->gradient == 1, xch) + waves - 1) / waves;   // workgroups across x
+    const int cols = two ? cgd::two_cols(p->bc_ylo == LBM_BC_PERIODIC) : cgd::wave_cols(p->gradient == 1, xch);
+    d.tiles_x = ((p->nx + cols - 1) / cols + waves - 1) / waves;   // workgroups across x
     d.tiles_y = (p->ny + strip - 1) / strip;
 }
 
@@ -322,7 +361,8 @@ using namespace cgi;
 
 static int upload_desc(lbm_ctx *c)
 {
-    hipError_t e = hipMemcpyAsync(c->d_desc, &c->desc, sizeof(SlotDesc), hipMemcpyHostToDevice, c->stream);
+    const SlotDesc both[2] = {c->desc, c->desc2};
+    hipError_t e = hipMemcpyAsync(c->d_desc, both, sizeof both, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     return e == hipSuccess ? LBM_OK : hip_fail(c, e, "uploading the lattice descriptor");
 }
@@ -350,6 +390,16 @@ static int replan(lbm_ctx *c)
     c->desc.active_steps = INT_MAX;
     c->tiles = c->desc.tiles_x * c->desc.tiles_y;
     c->tx = tx;
+    const long long nodes = (long long)c->p.nx * c->p.ny;
+    c->two = c->xch_req < 0 && plan_two(nodes, c->p.storage, var, c->p.ny);
+    c->desc2 = c->desc;
+    if (c->two) {
+        c->tx2 = two_tx(c->p.nx, c->tx_req);
+        set_geometry(c->desc2, &c->p, c->lay, c->tx2,
+                     plan_two_strip(&c->p, nodes, (long long)two_waves(&c->p) * c->p.ny, c->strip_req), false,
+                     true);
+        c->tiles2 = c->desc2.tiles_x * c->desc2.tiles_y;
+    }
     drop_graphs(c);
     return upload_desc(c);
 }
@@ -373,7 +423,7 @@ size_t lbm_bytes_required(const lbm_params *p)
     if (validate(p, m) != LBM_OK) return 0;
     const Layout L = layout(p);
     const size_t n = (size_t)p->nx * p->ny;
-    return 2 * L.buf_bytes + 5 * n * sizeof(float) + (size_t)p->ny + sizeof(SlotDesc) +
+    return 2 * L.buf_bytes + 5 * n * sizeof(float) + (size_t)p->ny + 2 * sizeof(SlotDesc) +
            (size_t)(cgd::moments_blocks((long long)n) * 9 + 9) * sizeof(double);
 }
 
@@ -428,7 +478,7 @@ static int create_common(const lbm_params *p, void *stream, void *ba, void *bb, 
         hipMalloc(&c->d_partial, (size_t)nb * 9 * sizeof(double)) != hipSuccess ||
         hipMalloc(&c->d_out, 9 * sizeof(double)) != hipSuccess ||
         hipMalloc(&c->d_inlet, (size_t)p->ny) != hipSuccess ||
-        hipMalloc(&c->d_desc, sizeof(SlotDesc)) != hipSuccess)
+        hipMalloc(&c->d_desc, 2 * sizeof(SlotDesc)) != hipSuccess)
         return bail(LBM_E_NOMEM, "hipMalloc of the work buffers failed");
     std::vector<int8_t> red((size_t)p->ny, 1);
     if ((e = hipMemcpy(c->d_inlet, red.data(), red.size(), hipMemcpyHostToDevice)) != hipSuccess)
@@ -537,9 +587,16 @@ int lbm_set_inlet_color(lbm_ctx *c, const int8_t *color_y)
     return e == hipSuccess ? LBM_OK : hip_fail(c, e, "inlet colour upload");
 }
 
-static const int kGraphSteps = 32;   // steps per captured graph (even)
+static const int kGraphSteps = 32;   // steps per captured graph (a multiple of 4)
 
 static int ctx_variant(const lbm_ctx *c) { return cgd::step_variant(c->desc) | (c->xch ? cgd::KV_XCH : 0); }
+
+// One launch at parity `par` on stream s: two steps, or one
+static hipError_t ctx_launch(lbm_ctx *c, bool two, int par, hipStream_t s)
+{
+    if (two) return cgd::launch_step(c->p.storage, c->tx2, c->d_desc + 1, 1, c->tiles2, par, 0, s, cgd::KV_TWO);
+    return cgd::launch_step(c->p.storage, c->tx, c->d_desc, 1, c->tiles, par, 0, s, ctx_variant(c));
+}
 
 static int build_graph(lbm_ctx *c, int parity)
 {
@@ -547,9 +604,8 @@ static int build_graph(lbm_ctx *c, int parity)
     hipError_t e = hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(c, e, "hipStreamBeginCapture");
     hipError_t le = hipSuccess;
-    for (int j = 0; j < kGraphSteps && le == hipSuccess; ++j)
-        le = cgd::launch_step(c->p.storage, c->tx, c->d_desc, 1, c->tiles, (parity + j) & 1, 0, c->cap_stream,
-                              ctx_variant(c));
+    for (int j = 0; j < (c->two ? kGraphSteps / 2 : kGraphSteps) && le == hipSuccess; ++j)
+        le = ctx_launch(c, c->two, (parity + j) & 1, c->cap_stream);
     e = hipStreamEndCapture(c->cap_stream, &graph);
     if (le != hipSuccess || e != hipSuccess) {
         if (graph) (void)hipGraphDestroy(graph);
@@ -580,9 +636,17 @@ int lbm_step(lbm_ctx *c, int64_t n)
         c->steps += kGraphSteps;
         n -= kGraphSteps;
     }
+    // two-step launches go in pairs, so that the state stays in the buffer of
+    // the step counter's parity
+    for (; c->two && n >= 4; n -= 4) {
+        const int par = (int)(c->steps & 1);
+        hipError_t e = ctx_launch(c, true, par, c->stream);
+        if (e == hipSuccess) e = ctx_launch(c, true, par ^ 1, c->stream);
+        if (e != hipSuccess) return hip_fail(c, e, "step launch");
+        c->steps += 4;
+    }
     for (; n > 0; --n) {
-        hipError_t e = cgd::launch_step(c->p.storage, c->tx, c->d_desc, 1, c->tiles, (int)(c->steps & 1), 0, c->stream,
-                                        ctx_variant(c));
+        hipError_t e = ctx_launch(c, false, (int)(c->steps & 1), c->stream);
         if (e != hipSuccess) return hip_fail(c, e, "step launch");
         c->steps++;
     }
@@ -789,6 +853,11 @@ struct BatchGroup {
     long long nodes = 0;
     int variant = 0;                    // step-kernel variant of its launches (one per group, KV_XCH included)
     int tx = 0;                         // threads per workgroup
+    // two steps per launch (KV_TWO) wherever a turn has enough of them: its
+    // own table of lattice descriptors, behind the other one
+    bool two = false;
+    std::vector<SlotDesc> slots2;
+    int tiles2 = 0, tx2 = 0;
     hipGraphExec_t graph[2] = {nullptr, nullptr};
 };
 
@@ -868,16 +937,22 @@ int lbm_batch_create(lbm_ctx *const *ctxs, int32_t n, int32_t tile_x, void *hip_
     b->groups.resize(ngroups);
     // strips are planned for what shares the chip: the group, and the group
     // the other lane steps beside it (two groups of the batch at a time)
-    long long pair_nodes = 0;
+    long long pair_nodes = 0, pair_rows = 0;   // pair_rows: wavefronts across times rows, two-step launches
     {
-        std::vector<long long> gn;
+        std::vector<long long> gn, gr;
         for (int gi = 0; gi < ngroups; ++gi) {
-            long long nodes = 0;
-            for (int i = first[gi]; i < first[gi + 1]; ++i) nodes += (long long)ctxs[i]->p.nx * ctxs[i]->p.ny;
+            long long nodes = 0, rows = 0;
+            for (int i = first[gi]; i < first[gi + 1]; ++i) {
+                nodes += (long long)ctxs[i]->p.nx * ctxs[i]->p.ny;
+                rows += (long long)two_waves(&ctxs[i]->p) * ctxs[i]->p.ny;
+            }
             gn.push_back(nodes);
+            gr.push_back(rows);
         }
         std::sort(gn.begin(), gn.end());
+        std::sort(gr.begin(), gr.end());
         pair_nodes = gn.back() + (ngroups > 1 ? gn[ngroups - 2] : 0);
+        pair_rows = gr.back() + (ngroups > 1 ? gr[ngroups - 2] : 0);
     }
     for (int gi = 0; gi < ngroups; ++gi) {
         BatchGroup &G = b->groups[gi];
@@ -895,8 +970,23 @@ int lbm_batch_create(lbm_ctx *const *ctxs, int32_t n, int32_t tile_x, void *hip_
         G.tx = gp.tx;
         G.variant = gp.variant;
         const bool xch = gp.variant & cgd::KV_XCH;
+        int min_ny = INT_MAX;
+        for (int i = first[gi]; i < first[gi + 1]; ++i) min_ny = std::min(min_ny, ctxs[i]->p.ny);
+        G.two = plan_two(pair_nodes, b->storage, kind[first[gi]], min_ny);
+        G.tx2 = two_tx(min_nx, tile_x);
+        long long tiles2 = 0;
         for (int i = first[gi]; i < first[gi + 1]; ++i) {
             lbm_ctx *c = ctxs[i];
+            if (G.two) {
+                SlotDesc d = c->desc;
+                set_geometry(d, &c->p, c->lay, G.tx2,
+                             plan_two_strip(&c->p, pair_nodes, pair_rows, c->strip_req), false, true);
+                d.tile_begin = (int)tiles2;
+                d.active_steps = INT_MAX;
+                if (c->steps & 1) std::swap(d.buf[0], d.buf[1]);
+                tiles2 += (long long)d.tiles_x * d.tiles_y;
+                G.slots2.push_back(d);
+            }
             SlotDesc d = c->desc;
             set_geometry(d, &c->p, c->lay, G.tx, 1, xch);
             set_geometry(d, &c->p, c->lay, G.tx,
@@ -908,11 +998,12 @@ int lbm_batch_create(lbm_ctx *const *ctxs, int32_t n, int32_t tile_x, void *hip_
             tiles += (long long)d.tiles_x * d.tiles_y;
             G.slots.push_back(d);
         }
-        if (tiles > INT_MAX / 2) {
+        if (tiles > INT_MAX / 2 || tiles2 > INT_MAX / 2) {
             lbm_batch_destroy(b);
             return fail(nullptr, LBM_E_INVAL, "batch too large");
         }
         G.tiles = (int)tiles;
+        G.tiles2 = (int)tiles2;
     }
     for (int i = 0; i < n; ++i) {
         b->ctx.push_back(ctxs[i]);
@@ -939,7 +1030,7 @@ int lbm_batch_create(lbm_ctx *const *ctxs, int32_t n, int32_t tile_x, void *hip_
         if (std::find(b->ctx_streams.begin(), b->ctx_streams.end(), c->stream) == b->ctx_streams.end())
             b->ctx_streams.push_back(c->stream);
     for (auto &G : b->groups)
-        if ((e = hipMalloc(&G.d_slots, G.slots.size() * sizeof(SlotDesc))) != hipSuccess) {
+        if ((e = hipMalloc(&G.d_slots, (G.slots.size() + G.slots2.size()) * sizeof(SlotDesc))) != hipSuccess) {
             G.d_slots = nullptr;
             lbm_batch_destroy(b);
             return fail(nullptr, LBM_E_DEVICE, std::string("batch: ") + hipGetErrorString(e));
@@ -948,6 +1039,9 @@ int lbm_batch_create(lbm_ctx *const *ctxs, int32_t n, int32_t tile_x, void *hip_
     for (auto *c : b->ctx) (void)hipStreamSynchronize(c->stream);
     for (auto &G : b->groups) {
         e = hipMemcpy(G.d_slots, G.slots.data(), G.slots.size() * sizeof(SlotDesc), hipMemcpyHostToDevice);
+        if (e == hipSuccess && G.two)
+            e = hipMemcpy(G.d_slots + G.slots.size(), G.slots2.data(), G.slots2.size() * sizeof(SlotDesc),
+                          hipMemcpyHostToDevice);
         if (e != hipSuccess) {
             lbm_batch_destroy(b);
             return fail(nullptr, LBM_E_DEVICE, std::string("batch: ") + hipGetErrorString(e));
@@ -957,15 +1051,22 @@ int lbm_batch_create(lbm_ctx *const *ctxs, int32_t n, int32_t tile_x, void *hip_
     return LBM_OK;
 }
 
+// One launch of a group at parity `par` on stream s: two steps, or one
+static hipError_t group_launch(lbm_batch *b, BatchGroup &G, bool two, int par, hipStream_t s)
+{
+    const int n = (int)G.slots.size();
+    if (two) return cgd::launch_step(b->storage, G.tx2, G.d_slots + n, n, G.tiles2, par, 0, s, cgd::KV_TWO);
+    return cgd::launch_step(b->storage, G.tx, G.d_slots, n, G.tiles, par, 0, s, G.variant);
+}
+
 static int batch_graph(lbm_batch *b, BatchGroup &G, int parity)
 {
     hipGraph_t graph = nullptr;
     hipError_t e = hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return bfail(b, LBM_E_DEVICE, std::string("capture: ") + hipGetErrorString(e));
     hipError_t le = hipSuccess;
-    for (int j = 0; j < kGraphSteps && le == hipSuccess; ++j)
-        le = cgd::launch_step(b->storage, G.tx, G.d_slots, (int)G.slots.size(), G.tiles, (parity + j) & 1, 0,
-                              b->cap_stream, G.variant);
+    for (int j = 0; j < (G.two ? kGraphSteps / 2 : kGraphSteps) && le == hipSuccess; ++j)
+        le = group_launch(b, G, G.two, (parity + j) & 1, b->cap_stream);
     e = hipStreamEndCapture(b->cap_stream, &graph);
     if (le != hipSuccess || e != hipSuccess) {
         if (graph) (void)hipGraphDestroy(graph);
@@ -996,9 +1097,13 @@ static int group_steps(lbm_batch *b, BatchGroup &G, int64_t start, int64_t n, hi
         t += kGraphSteps;
         n -= kGraphSteps;
     }
+    for (; G.two && n >= 4; n -= 4, t += 4) {   // in pairs, as in lbm_step
+        hipError_t e = group_launch(b, G, true, (int)(t & 1), stream);
+        if (e == hipSuccess) e = group_launch(b, G, true, (int)(t & 1) ^ 1, stream);
+        if (e != hipSuccess) return bfail(b, LBM_E_DEVICE, std::string("launch: ") + hipGetErrorString(e));
+    }
     for (; n > 0; --n, ++t) {
-        hipError_t e = cgd::launch_step(b->storage, G.tx, G.d_slots, (int)G.slots.size(), G.tiles, (int)(t & 1), 0,
-                                        stream, G.variant);
+        hipError_t e = group_launch(b, G, false, (int)(t & 1), stream);
         if (e != hipSuccess) return bfail(b, LBM_E_DEVICE, std::string("launch: ") + hipGetErrorString(e));
     }
     return LBM_OK;

@@ -36,8 +36,9 @@ struct lbm_ctx {
     size_t buf_bytes = 0;
     cgi::Layout lay{};
     int8_t *d_inlet = nullptr;
-    cgd::SlotDesc desc{};
-    cgd::SlotDesc *d_desc = nullptr;
+    cgd::SlotDesc desc{};               // geometry of the single-step launch
+    cgd::SlotDesc desc2{};              // and of the two-step launch (two)
+    cgd::SlotDesc *d_desc = nullptr;    // both on the device
     float *d_fields = nullptr;          // 5 n floats: init input / moments output
     double *d_partial = nullptr;
     double *d_out = nullptr;
@@ -46,6 +47,8 @@ struct lbm_ctx {
     int tx_req = 0, strip_req = 0;      // lbm_set_launch requests (0: planned)
     int xch_req = -1;                   // lbm_set_exchange request (-1: planned)
     bool xch = false;                   // planned: the exchange flavour (KV_XCH)
+    bool two = false;                   // planned: two steps per launch (KV_TWO) wherever a call has enough of them
+    int tx2 = 0, tiles2 = 0;
     hipGraphExec_t graph[2] = {nullptr, nullptr};
     int graph_len = 0;
     std::string err;
@@ -63,6 +66,15 @@ int xch_tx(int nx, int ny, int variant);
 // FP32 launches take the exchange flavour of the step (KV_XCH).
 constexpr size_t kXchBytes = 256ull << 20;
 bool plan_exchange(size_t bytes, int storage, int variant);
+// Two steps per launch (KV_TWO), see cg_capi.cpp: whether lattices of this
+// storage and variant take it when `nodes` nodes are in flight together, the
+// threads per workgroup, and the rows per strip that let the wavefronts of all
+// lattices in flight (`wave_rows`: the sum of two_waves x ny over them) be resident
+// at once.
+bool plan_two(long long nodes, int storage, int variant, int ny);
+int two_tx(int nx, int req);
+int two_waves(const lbm_params *p);
+int plan_two_strip(const lbm_params *p, long long nodes, long long wave_rows, int req);
 // `paired`: the launch shares the chip with a second one (a batch's lanes);
 // `xch`: exchange flavour.
 int plan_strip(long long nodes, int ny, int tiles_x, int storage, int req, bool paired = false, bool xch = false);
@@ -94,6 +106,6 @@ inline std::vector<int> cache_groups(const std::vector<size_t> &bytes, const std
 {
     return cgs::cache_groups(bytes, kind, budget, min_groups);
 }
-void set_geometry(cgd::SlotDesc &d, const lbm_params *p, const Layout &L, int tx, int strip, bool xch);
+void set_geometry(cgd::SlotDesc &d, const lbm_params *p, const Layout &L, int tx, int strip, bool xch, bool two = false);
 
 }  // namespace cgi

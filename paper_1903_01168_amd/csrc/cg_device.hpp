@@ -55,6 +55,12 @@ enum : int { ST_F32 = 0, ST_F16S = 1, ST_BF16S = 2 };
 // nodes of its workgroup.
 __host__ __device__ constexpr int wave_halo(bool iso, bool xch) { return xch && !iso ? 0 : (iso ? 3 : 2); }
 __host__ __device__ constexpr int wave_cols(bool iso, bool xch) { return 64 - 2 * wave_halo(iso, xch); }
+// Two steps per launch: each step takes the reach of its gradient (1 column)
+// and its pull (1) from the lanes on either side, except that the first step's
+// pull reads any column from memory; rows next to a wall reach one column
+// further in each step (ghost values).
+__host__ __device__ constexpr int two_halo(bool yper) { return yper ? 3 : 5; }
+__host__ __device__ constexpr int two_cols(bool yper) { return 64 - 2 * two_halo(yper); }
 
 // ------------------------------------------------------------- descriptor --
 // One lattice ("slot") of a launch.  Built on the host; read with scalar loads.
@@ -140,8 +146,7 @@ template <> struct Codec<ST_F32> {
 //       (equal for both fluids: the phases' alphas make rho0_k (1 - alpha_k)
 //       the same, Sec. 2.1.1).
 // Decoding: N_i = m_c + q 2^-12 max(rho0), N^r_i = g N_i, N^b_i = (1 - g) N_i
-// (one fused multiply-add from N_i); a node's colour masses are the exact FP64
-// sums sum_i N^r_i and sum_i N_i - sum_i N^r_i plus the rest populations.
+// (one fused multiply-add from N_i).
 // The colour-blind population, which carries mass and momentum, is held as a
 // small deviation with FP16's relative precision in bulk and interface nodes
 // alike, and the colour split with a uniform 1.5e-5 quantum; a per-colour
@@ -167,11 +172,9 @@ __device__ __forceinline__ uint32_t mix32(uint32_t h)
     h ^= h >> 16;
     return h;
 }
-// j-th dither of a node: a Weyl sequence from the node's hashed seed whose
-// increment is the golden ratio in its high and in its low 16 bits, so that
-// either half spreads evenly: one word dithers a pair (the high bits its
-// deviation, the low 16 its share)
-__device__ __forceinline__ uint32_t weyl(uint32_t seed, int j) { return seed + (uint32_t)j * 0x9e379e37u; }
+// j-th dither of a node: a Weyl sequence (golden-ratio increments) from the
+// node's hashed seed; its high bits are the ones used, and they spread evenly
+__device__ __forceinline__ uint32_t weyl(uint32_t seed, int j) { return seed + (uint32_t)j * 0x9e3779b9u; }
 
 typedef _Float16 cg_h2 __attribute__((ext_vector_type(2)));
 typedef __bf16 cg_b2 __attribute__((ext_vector_type(2)));
@@ -246,63 +249,51 @@ __device__ __forceinline__ void dec_pair(const SlotDesc &S, int c, uint16_t q, u
     split(N, u, nr, nb);
 }
 
-// Share of a pair as 16.16 fixed point (65535 << 16 for a share of 1), dithered
-// by a word's low 16 bits (sr = false: rounded to nearest); u = its high half.
-// 0 and 65535 << 16 keep their high half under any dither.
-constexpr float kShareOne = 65535.f * 65536.f;
-__device__ __forceinline__ uint32_t dither_share(uint32_t t, uint32_t rnd, bool sr)
-{
-    return t + (sr ? rnd & 0xffffu : 0x8000u);
-}
-// float share times kShareOne to fixed point: clamped to [0, 1]; NaN gives 0
-__device__ __forceinline__ uint32_t fix_share(float ts) { return (uint32_t)__builtin_amdgcn_fmed3f(ts, 0.f, kShareOne); }
-
-// Encode a pair given its colour-blind population n and its undithered share
-// (fix_share); N, nr: the colour-blind and red populations that the store
-// leaves behind.  rnd: dither (high bits for the deviation, low 16 for the
-// share); sr = false: round to nearest.
+// Encode a pair; returns the decoded values the store leaves behind.
+// rnd: dither (high bits for the deviation, low 16 bits for the share);
+// sr = false: round to nearest.
 template <int ST>
-__device__ __forceinline__ void enc_pair(const SlotDesc &S, int c, float n, uint32_t t, uint32_t rnd, bool sr, uint16_t &q,
-                                         uint16_t &u, float &N, float &nr)
+__device__ __forceinline__ void enc_pair(const SlotDesc &S, int c, float vr, float vb, uint32_t rg, uint32_t rq, bool sr,
+                                         uint16_t &q, uint16_t &u, float &nr, float &nb)
 {
-    u = (uint16_t)(dither_share(t, rnd, sr) >> 16);
+    const float n = vr + vb;
+    float g = vr * __builtin_amdgcn_rcpf(n);
+    g = g > 0.f ? (g < 1.f ? g : 1.f) : 0.f;          // NaN -> 0 (its N stays NaN)
+    g = vb == 0.f ? 1.f : (vr == 0.f ? 0.f : g);       // an absent colour stays exactly absent
+    // dither in [0, 1) from the top 23 bits (as the mantissa of a number in [1, 2))
+    const float dith = sr ? __uint_as_float(0x3f800000u | (rg >> 9)) - 1.f : 0.5f;
+    const uint32_t ui = (uint32_t)__builtin_fmaf(g, 65535.f, dith);   // g in [0,1]: 0 .. 65535
+    u = (uint16_t)(ui > 65535u ? 65535u : ui);
     const float x = (n - S.mref[c]) * S.dscale;
-    q = sr ? Codec<ST>::enc_q(x, rnd) : Codec<ST>::enc_q_nearest(x);
-    N = __builtin_fmaf(Codec<ST>::dec_q(q), S.dmul, S.mref[c]);
-    nr = share(u) * N;
-}
-// Share of a pair of populations; an absent colour stays exactly absent.
-__device__ __forceinline__ uint32_t pair_share(float vr, float vb)
-{
-    const uint32_t t = fix_share(vr * __builtin_amdgcn_rcpf(vr + vb) * kShareOne);
-    return vb == 0.f ? (uint32_t)kShareOne : (vr == 0.f ? 0u : t);
+    q = sr ? Codec<ST>::enc_q(x, rq) : Codec<ST>::enc_q_nearest(x);
+    split(__builtin_fmaf(Codec<ST>::dec_q(q), S.dmul, S.mref[c]), u, nr, nb);
 }
 
 // FP32 rest population of a colour: the value itself or its deviation from
 // rest0, whichever is smaller in magnitude (finer FP32 quantum for a minority
 // and for a majority colour alike); the mantissa's last bit tells which.  The
 // value is rounded onto the FP32 numbers that carry that last bit (a grid of
-// two ulps), stochastically with the 30 high bits of rnd (half: to nearest):
+// two ulps), stochastically with the dither r01 in [0, 1) (0.5: to nearest):
 // forcing the bit onto a rounded value would bias the rest, and with it the
-// colour mass, at every node and step.  The rounding is integer arithmetic on
-// the FP64 bits: an FP32 ulp is 2^29 there, so adding 30 random bits to the
-// offset from the grid and truncating rounds up with the right probability.
-constexpr uint32_t kRestHalf = 0x80000000u;
-__device__ __forceinline__ uint32_t enc_rest(double v, float ref, uint32_t rnd)
+// colour mass, at every node and step.
+__device__ __forceinline__ uint32_t enc_rest(double v, float ref, double r01)
 {
-    const double dev = v - (double)ref;
-    const bool fl = fabs(dev) < fabs(v);
-    const uint64_t bits = (uint64_t)__double_as_longlong(fl ? dev : v);
-    const uint32_t flag = fl ? 1u : 0u;
-    const uint32_t hi = (uint32_t)(bits >> 32) & 0x7fffffffu, sign = (uint32_t)(bits >> 32) & 0x80000000u;
-    const uint64_t a = ((uint64_t)hi << 32) | (uint32_t)bits;
-    const uint64_t g = a + (uint64_t)(rnd >> 2) - ((uint64_t)flag << 29);
-    uint32_t m = ((uint32_t)(g >> 29) - (896u << 23)) & ~1u;   // exponent bias 1023 -> 127
-    // below the normal FP32 range: the smallest magnitude of the grid; beyond
-    // it (only after the lattice has gone non-finite): infinity or NaN
-    if (hi - 0x38100000u >= 0x47e00000u - 0x38100000u)
-        m = hi < 0x38100000u ? 0u : __float_as_uint((float)__longlong_as_double((long long)a)) & ~1u;
-    return m | flag | sign;
+    const uint32_t flag = fabs(v - (double)ref) < fabs(v) ? 1u : 0u;
+    const double t = flag ? v - (double)ref : v;
+    const double a = fabs(t);
+    const uint32_t m = __float_as_uint((float)a);
+    uint32_t lo, hi;
+    if ((m & 1u) == flag) {
+        if ((double)__uint_as_float(m) <= a) { lo = m; hi = m + 2u; }
+        else { lo = m - 2u; hi = m; }
+    } else {
+        lo = m - 1u;
+        hi = m + 1u;
+    }
+    if (lo > hi) lo = flag;   // below the smallest magnitude of the grid
+    const double vlo = (double)__uint_as_float(lo), vhi = (double)__uint_as_float(hi);
+    const uint32_t mm = (a - vlo) > r01 * (vhi - vlo) ? hi : lo;
+    return mm | (t < 0.0 ? 0x80000000u : 0u);
 }
 // decoded rest population (FP32) and its exact value (FP64)
 __device__ __forceinline__ float dec_rest(uint32_t b, float ref, double &exact)
@@ -677,17 +668,14 @@ __device__ __forceinline__ Node finish(const SlotDesc &S, const Raw18<ST> &raw, 
         const float r0 = dec_rest(raw.r0[0], S.rest0[0], rho[0]);
         const float b0 = dec_rest(raw.r0[1], S.rest0[1], rho[1]);
         nd.n[0] = r0 + b0;
-        double sn = 0.0, sr = 0.0;
 #pragma unroll
         for (int i = 1; i < 9; ++i) {
-            const float N = __builtin_fmaf(C::dec_q(raw.v[i]), S.dmul, S.mref[vclass(i)]);
-            const float nr = share(raw.v[9 + i]) * N;
+            float N, nr, nb;
+            dec_pair<ST>(S, vclass(i), raw.v[i], raw.v[9 + i], N, nr, nb);
             nd.n[i] = N;
-            sn = i == 1 ? (double)N : sn + (double)N;
-            sr = i == 1 ? (double)nr : sr + (double)nr;
+            rho[0] += (double)nr;
+            rho[1] += (double)nb;
         }
-        rho[0] += sr;
-        rho[1] += sn - sr;
     } else {
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
@@ -772,57 +760,14 @@ __device__ __forceinline__ Node finish(const SlotDesc &S, const Raw18<ST> &raw, 
 struct NodeAt {
     uint32_t col, rcol, row, pos;
 };
+// Column offset beyond every resource (a colour half stays below 4 GiB - 4096):
+// the hardware drops the store of a lane that carries it.
+constexpr uint32_t kNoStore = 0xfffff000u;
 template <int ST>
 __device__ __forceinline__ NodeAt node_at(const SlotDesc &S, int x, int y)
 {
     return NodeAt{col_off<ST>(x), rest_col_off<ST>(x), (uint32_t)y * (uint32_t)S.row_bytes,
                   2u * ((uint32_t)y * (uint32_t)S.pitch + (uint32_t)x)};
-}
-
-// The two rest populations of a node in 16-bit storage.
-__device__ __forceinline__ void store_rest(const SlotDesc &S, const Halves &h, const NodeAt &at, double r, double b,
-                                           uint32_t seed)
-{
-    const uint32_t r1 = CG_CODEC_SR ? weyl(seed, 9) : kRestHalf, r2 = CG_CODEC_SR ? weyl(seed, 10) : kRestHalf;
-    __builtin_amdgcn_raw_buffer_store_b32(enc_rest(r, S.rest0[0], r1), h.r[0], (int)at.rcol, (int)at.row, CG_STORE_POLICY);
-    __builtin_amdgcn_raw_buffer_store_b32(enc_rest(b, S.rest0[1], r2), h.r[1], (int)at.rcol, (int)at.row, CG_STORE_POLICY);
-}
-
-// Store the 18 post-recolouring populations of one node; mr, mb: the colour
-// masses the node must hold (exact FP64).  16-bit storage: the eight moving
-// pairs are encoded (see the codec), the colour masses of what they decode to
-// summed exactly in FP64, and each FP32 rest population takes the remainder of
-// its colour's mass, so the stored colour masses of the node are exact to the
-// rounding of one FP32 value each.
-template <int ST>
-__device__ __forceinline__ void store18(const SlotDesc &S, const Halves &h, const NodeAt &at, const float *outr,
-                                        const float *outb, double mr, double mb)
-{
-    using C = Codec<ST>;
-    if constexpr (ST == ST_F32) {
-#pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            C::store(outr[i], h.r[0], at.col, plane_off<ST>(i) + at.row, S, 0, vclass(i));
-            C::store(outb[i], h.r[1], at.col, plane_off<ST>(i) + at.row, S, 1, vclass(i));
-        }
-    } else {
-        // one seed per node from its position and two of the values stored
-        const uint32_t seed = mix32(at.pos ^ __float_as_uint(outr[1]) ^
-                                    __builtin_rotateleft32(__float_as_uint(outb[5]), 13));
-        double sn = 0.0, sr = 0.0;
-#pragma unroll
-        for (int i = 1; i < 9; ++i) {
-            uint16_t q, u;
-            float N, nr;
-            enc_pair<ST>(S, vclass(i), outr[i] + outb[i], pair_share(outr[i], outb[i]), weyl(seed, i), CG_CODEC_SR != 0, q, u,
-                         N, nr);
-            sn += (double)N;
-            sr += (double)nr;
-            C::put(q, h.r[0], at.col, plane_off<ST>(i) + at.row);
-            C::put(u, h.r[1], at.col, plane_off<ST>(i) + at.row);
-        }
-        store_rest(S, h, at, mr - sr, mb - (sn - sr), seed);
-    }
 }
 
 // Store 18 given populations, rounding to nearest without dither, the rest
@@ -842,14 +787,14 @@ __device__ __forceinline__ void store18_nearest(const SlotDesc &S, const Halves 
 #pragma unroll
         for (int i = 1; i < 9; ++i) {
             uint16_t q, u;
-            float N, nr;
-            enc_pair<ST>(S, vclass(i), outr[i] + outb[i], pair_share(outr[i], outb[i]), 0u, false, q, u, N, nr);
+            float nr, nb;
+            enc_pair<ST>(S, vclass(i), outr[i], outb[i], 0u, 0u, false, q, u, nr, nb);
             C::put(q, h.r[0], at.col, plane_off<ST>(i) + at.row);
             C::put(u, h.r[1], at.col, plane_off<ST>(i) + at.row);
         }
-        __builtin_amdgcn_raw_buffer_store_b32(enc_rest((double)outr[0], S.rest0[0], kRestHalf), h.r[0], (int)at.rcol,
+        __builtin_amdgcn_raw_buffer_store_b32(enc_rest((double)outr[0], S.rest0[0], 0.5), h.r[0], (int)at.rcol,
                                               (int)at.row, CG_STORE_POLICY);
-        __builtin_amdgcn_raw_buffer_store_b32(enc_rest((double)outb[0], S.rest0[1], kRestHalf), h.r[1], (int)at.rcol,
+        __builtin_amdgcn_raw_buffer_store_b32(enc_rest((double)outb[0], S.rest0[1], 0.5), h.r[1], (int)at.rcol,
                                               (int)at.row, CG_STORE_POLICY);
     }
 }
@@ -886,15 +831,25 @@ __device__ __forceinline__ float refined_rcp(float x)
     return __builtin_fmaf(r, __builtin_fmaf(-x, r, 1.f), r);
 }
 
-// Colour field, Sec. 2.1.1 eq. (color_field): +1 in pure red.
+// Colour field, Sec. 2.1.1 eq. (color_field): +1 in pure red.  Formed from
+// the minority's volume fraction m as +-(1 - 2 m): exactly +-1 in a pure fluid
+// and wherever a trace of the other colour is below the field's resolution, so
+// that the gradient vanishes there and its terms are skipped ((a - b) / (a + b)
+// left a noise of an ulp around -1 in such regions).
+template <int ST>
 __device__ __forceinline__ float color_field(const SlotDesc &S, float rr, float rb)
 {
     // no contraction: every lane computing a column's colour field (its owner
     // or a halo lane) must round it the same way
 #pragma clang fp contract(off)
     const float a = rr * S.inv_rho0[0], b = rb * S.inv_rho0[1];
-    const float psi = (a - b) * fast_rcp(a + b);
-    return b == 0.f ? 1.f : (a == 0.f ? -1.f : psi);   // exactly +-1 in a pure fluid
+    if constexpr (rest32<ST>()) {
+        const float psi = (a - b) * fast_rcp(a + b);
+        return b == 0.f ? 1.f : (a == 0.f ? -1.f : psi);
+    }
+    const float m = (a < b ? a : b) * fast_rcp(a + b);
+    const float psi = __builtin_fmaf(-2.f, m, 1.f);
+    return a < b ? -psi : psi;
 }
 
 // Momentum with the half-force shift of Guo forcing.
@@ -926,6 +881,45 @@ __device__ __forceinline__ float omega_eff(const SlotDesc &S, float psi)
     if (psi > 0.f) return S.chi + psi * (S.eta + S.kappa * psi);
     if (psi >= -S.delta) return S.chi + psi * (S.lam + S.nu * psi);
     return S.omega_b;
+}
+
+// M x for the D2Q9 moment basis of Appendix B (rows: rho, e, eps, jx, qx,
+// jy, qy, pxx, pxy).
+__device__ __forceinline__ void mrt_fwd(const float *f, float *m)
+{
+    const float a = f[1] + f[2] + f[3] + f[4];
+    const float d = f[5] + f[6] + f[7] + f[8];
+    m[0] = f[0] + a + d;
+    m[1] = -4.f * f[0] - a + 2.f * d;
+    m[2] = 4.f * f[0] - 2.f * a + d;
+    const float dx = f[5] - f[6] - f[7] + f[8];
+    const float dy = f[5] + f[6] - f[7] - f[8];
+    m[3] = (f[1] - f[3]) + dx;
+    m[4] = -2.f * (f[1] - f[3]) + dx;
+    m[5] = (f[2] - f[4]) + dy;
+    m[6] = -2.f * (f[2] - f[4]) + dy;
+    m[7] = (f[1] + f[3]) - (f[2] + f[4]);
+    m[8] = (f[5] + f[7]) - (f[6] + f[8]);
+}
+
+// M^{-1} m = M^T diag(1/9, 1/36, 1/36, 1/6, 1/12, 1/6, 1/12, 1/4, 1/4) m
+__device__ __forceinline__ void mrt_inv(const float *m, float *f)
+{
+    const float a0 = m[0] * (1.f / 9.f), a1 = m[1] * (1.f / 36.f), a2 = m[2] * (1.f / 36.f);
+    const float a3 = m[3] * (1.f / 6.f), a4 = m[4] * (1.f / 12.f), a5 = m[5] * (1.f / 6.f);
+    const float a6 = m[6] * (1.f / 12.f), a7 = m[7] * 0.25f, a8 = m[8] * 0.25f;
+    f[0] = a0 - 4.f * a1 + 4.f * a2;
+    const float ax = a0 - a1 - 2.f * a2;
+    f[1] = ax + a3 - 2.f * a4 + a7;
+    f[3] = ax - a3 + 2.f * a4 + a7;
+    f[2] = ax + a5 - 2.f * a6 - a7;
+    f[4] = ax - a5 + 2.f * a6 - a7;
+    const float dg = a0 + 2.f * a1 + a2;
+    const float px = a3 + a4, py = a5 + a6;
+    f[5] = dg + px + py + a8;
+    f[6] = dg - px + py - a8;
+    f[7] = dg - px - py + a8;
+    f[8] = dg + px - py - a8;
 }
 
 // Wetting (Sec. 2.4) at a node of the first (bottom) or last row next to a
@@ -1140,19 +1134,15 @@ __device__ __forceinline__ void recolor(const Post &P, int i, float &r, float &b
     b = P.red_minor ? majo : mino;
 }
 
-// FP32 storage: split and store one node.  The rounding of the 18 outputs (of
-// the order of an ulp of the rest population, and the same at every node of a
-// uniform region) is measured in FP64 and returned to the four diagonal
-// populations of each colour, whose ulp is 16-32 times finer: per step, each
-// node conserves the mass of each colour to a few ulps of its smallest
-// populations.  POL: cache policy bits of the stores.
-template <int POL = CG_STORE_POLICY>
-__device__ __forceinline__ void store_f32_node(const Halves &h, const NodeAt &at, const Post &P, double mr, double mb)
+// FP32 storage: split one node and put its 18 populations (put(i, k, value)).
+// The rounding of the 18 outputs (of the order of an ulp of the rest
+// population, and the same at every node of a uniform region) is measured in
+// FP64 and returned to the four diagonal populations of each colour, whose ulp
+// is 16-32 times finer: per step, each node conserves the mass of each colour
+// to a few ulps of its smallest populations.
+template <class Put>
+__device__ __forceinline__ void put_f32_node(const Post &P, double mr, double mb, Put &&put)
 {
-    const auto put = [&](int i, int k, float v) {
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), h.r[k], (int)at.col,
-                                              (int)(plane_off<ST_F32>(i) + at.row), POL);
-    };
     float kr[4], kb[4];
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
@@ -1176,45 +1166,209 @@ __device__ __forceinline__ void store_f32_node(const Halves &h, const NodeAt &at
     }
 }
 
-// 16-bit storage: encode and store one node.  The share of direction i is
-// the red fraction of the node plus its segregation term over N**_i; where no
-// lane of a wavefront has one, every direction has the same share.
-template <int ST>
-__device__ __forceinline__ void store_16_node(const SlotDesc &S, const Halves &h, const NodeAt &at, const Post &P,
-                                              double mr, double mb)
+// The same to a population buffer.  POL: cache policy bits of the stores.
+template <int POL = CG_STORE_POLICY>
+__device__ __forceinline__ void store_f32_node(const Halves &h, const NodeAt &at, const Post &P, double mr, double mb)
 {
-#pragma clang fp contract(off)
-    using C = Codec<ST>;
-    const float c1 = (P.red_minor ? P.cmin : 1.f - P.cmin) * kShareOne;   // exactly 0 / kShareOne for an absent colour
-    uint32_t t[9];
-    const uint32_t t0 = fix_share(c1);
+    put_f32_node(P, mr, mb, [&](int i, int k, float v) {
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), h.r[k], (int)at.col,
+                                              (int)(plane_off<ST_F32>(i) + at.row), POL);
+    });
+}
+
+// The same of a lattice in 16-bit storage, direction by direction; each output
+// pair (post-recolouring red and blue populations) goes to sink(i, red, blue).
+// The encoder's dither is seeded by the bits of these outputs, so another
+// rounding anywhere in here is another sequence of dithers: the expressions
+// stay as they are.
+template <bool NSC = false, class Sink>
+__device__ __forceinline__ void collide_16(const SlotDesc &S, const Node &nd, float psi, float Fx, float Fy, Sink &&sink,
+                                        bool nsc = false, float dqx = 0.f, float dqy = 0.f)
+{
+    const float rr = nd.rr(), rb = nd.rb();
+    const float rho = rr + rb;
+    float ux, uy;
+    velocity(S, nd, rho, ux, uy);
+    const float w = omega_eff(S, psi);
+    const float uu = __builtin_fmaf(ux, ux, uy * uy);
+
+    float neq[9];     // N - N^(e)
+    const bool force = S.flags & F_FORCE;
+    const float gxr = rho * S.gx, gyr = rho * S.gy;
+    // Guo forcing source of direction i (force density rho g); evaluated only
+    // under the uniform branch of a forced lattice
+    auto guo = [&](int i) {
+        const float cu = cx(i) * ux + cy(i) * uy;
+        return wgt(i) * ((3.f * (cx(i) - ux) + 9.f * cu * cx(i)) * gxr + (3.f * (cy(i) - uy) + 9.f * cu * cy(i)) * gyr);
+    };
+    // Hermite equilibrium: the linear term of colour k carries the factor
+    // 1 + (3 c_s,k^2 - 1)(3 |c_i|^2 - 4) / 2; summed over the colours its
+    // density is rho + hco(i) K with K = sum_k rho_k (3 c_s,k^2 - 1)
+    const bool herm = NSC && nsc;
+    const float K = herm ? rr * S.k3[0] + rb * S.k3[1] : 0.f;
 #pragma unroll
-    for (int i = 1; i < 9; ++i) t[i] = t0;
-    if (P.gx != 0.f || P.gy != 0.f) {
-        const float k = P.red_minor ? kShareOne : -kShareOne;
-#pragma unroll
-        for (int i = 1; i < 9; ++i) t[i] = fix_share(__builtin_fmaf(P.seg(i) * k, __builtin_amdgcn_rcpf(P.n[i]), c1));
+    for (int i = 0; i < 9; ++i) {
+        const float cu = cx(i) * ux + cy(i) * uy;
+        const int c = vclass(i);
+        // N - N^(e) with the rest part subtracted by fused multiply-adds: the
+        // large rest populations of a heavy fluid never get rounded on their own
+        float t = __builtin_fmaf(-rr, S.phi[0][c], nd.n[i]);
+        t = __builtin_fmaf(-rb, S.phi[1][c], t);
+        // unit mass of the FP32 rest weights, and the exact mass of the node
+        if (i == 0) t -= rr * S.phi0_eps[0] + rb * S.phi0_eps[1] + nd.dm();
+        if (herm && i != 0)
+            neq[i] = t - wgt(i) * (3.f * cu * __builtin_fmaf(hco(i), K, rho) + rho * (4.5f * cu * cu - 1.5f * uu));
+        else
+            neq[i] = t - rho * wgt(i) * (3.f * cu + 4.5f * cu * cu - 1.5f * uu);
     }
-    // One seed per node from its position, one of the values stored and its
-    // exact colour masses, whose last bits carry the previous step's share
-    // dither: a steady node then draws anew every step (seeded by N** alone,
-    // which there takes a few values only, it repeated its rounding errors and
-    // the 64 x 64 bubble's colour mass drifted by 4e-7 in 20000 steps).
-    const uint64_t br = (uint64_t)__double_as_longlong(mr), bb = (uint64_t)__double_as_longlong(mb);
-    const uint32_t seed = mix32(at.pos ^ __float_as_uint(P.n[1]) ^ (uint32_t)(br >> 16) ^
-                                __builtin_rotateleft32((uint32_t)(bb >> 16), 13));
-    double sn = 0.0, sr = 0.0;
+    float ns[9];
+    if (S.flags & F_MRT) {
+        float m[9], q[9];
+        mrt_fwd(neq, m);
+        const float sl = S.mrt_lambda * w;
+        if (force) {
+            float G[9], mg[9];
+#pragma unroll
+            for (int i = 0; i < 9; ++i) G[i] = guo(i);
+            mrt_fwd(G, mg);
+#pragma unroll
+            for (int j = 0; j < 9; ++j) {
+                const float s = (j >= 7) ? w : sl;
+                q[j] = s * m[j] - (1.f - 0.5f * s) * mg[j];
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 9; ++j) q[j] = ((j >= 7) ? w : sl) * m[j];
+        }
+        if (herm) {
+            // source U = M^-1 C, C_1 = 3 (1 - s_1/2)(dQx/dx + dQy/dy),
+            // C_7 = (1 - s_7/2)(dQx/dx - dQy/dy): N* = N - M^-1 (q - C)
+            q[1] -= 3.f * (1.f - 0.5f * sl) * (dqx + dqy);
+            q[7] -= (1.f - 0.5f * w) * (dqx - dqy);
+        }
+        float dn[9];
+        mrt_inv(q, dn);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) ns[i] = nd.n[i] - dn[i];
+    } else {
+        if (force) {
+            const float hf = 1.f - 0.5f * w;
+#pragma unroll
+            for (int i = 0; i < 9; ++i) ns[i] = __builtin_fmaf(hf, guo(i), __builtin_fmaf(-w, neq[i], nd.n[i]));
+        } else {
+#pragma unroll
+            for (int i = 0; i < 9; ++i) ns[i] = __builtin_fmaf(-w, neq[i], nd.n[i]);
+        }
+    }
+
+    const float F2 = __builtin_fmaf(Fx, Fx, Fy * Fy);
+    // Recolouring split: the minority colour is computed from its own fraction
+    // (keeping its relative precision in the tails of an interface) and the
+    // majority colour as the difference, so that N^r + N^b = N** holds to the
+    // last bit and the colour-blind mass is untouched by the split.
+    const float irho = refined_rcp(rho);
+    const bool red_minor = rr < rb;
+    const float cmin = (red_minor ? rr : rb) * irho;    // 0 exactly for an absent colour
+    const float cmaj = (red_minor ? rb : rr) * irho;
+    const float sgn = red_minor ? 1.f : -1.f;           // the segregation term adds to red
+    // no gradient (|F| <= 1e-12): neither perturbation nor segregation.  Both
+    // forms are evaluated and selected per lane (uniform control flow, so that
+    // every store of a row is one instruction over the whole wavefront).
+    const bool pert = F2 > 1e-24f;
+    const float inv = pert ? __builtin_amdgcn_rsqf(F2) : 0.f;   // 1/|F|
+    const float Fm = F2 * inv;                                   // |F|
+    const float A = (S.flags & F_SIGMA) ? S.sigma94 * w : S.A;
+    const float seg = S.beta * cmin * cmaj;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+        const float fc = cx(i) * Fx + cy(i) * Fy;
+        const float nss = ns[i] + A * (wgt(i) * fc * fc * inv - bco(i) * Fm);
+        float sg = 0.f;
+        if (i != 0) {
+            const int c = vclass(i);
+            const float cosphi = fc * inv * (c == 1 ? 1.f : 0.70710678118654752f);
+            sg = seg * cosphi * (rr * S.phi[0][c] + rb * S.phi[1][c]);
+        }
+        const float mino_p = cmin * nss + sgn * sg;
+        const float majo_p = nss - mino_p;
+        const float mino_0 = cmin * ns[i];
+        const float majo_0 = ns[i] - mino_0;
+        const float mino = pert ? mino_p : mino_0;
+        const float majo = pert ? majo_p : majo_0;
+        sink(i, red_minor ? mino : majo, red_minor ? majo : mino);
+    }
+}
+
+// A sink that keeps the 18 outputs.
+struct Keep18 {
+    float r[9], b[9];
+    __device__ __forceinline__ void operator()(int i, float vr, float vb)
+    {
+        r[i] = vr;
+        b[i] = vb;
+    }
+};
+
+// 16-bit storage: encode one node and put its eight pairs (put(i, q, u)) and
+// its two FP32 rest populations (rest(k, bits)).  The eight moving pairs are
+// encoded (see the codec), the colour masses of what they decode to summed
+// exactly in FP64, and each FP32 rest population takes the remainder of its
+// colour's mass (mr, mb: exact FP64), so the stored colour masses of the node
+// are exact to the rounding of one FP32 value each.  pos: the node's position
+// (see NodeAt).
+template <int ST, class Put, class Rest>
+__device__ __forceinline__ void put_16_node(const SlotDesc &S, uint32_t pos, const float *outr, const float *outb,
+                                            double mr, double mb, Put &&put, Rest &&rest)
+{
+    // one seed per node from its position and two of the values stored
+    const uint32_t seed = mix32(pos ^ __float_as_uint(outr[1]) ^ __builtin_rotateleft32(__float_as_uint(outb[5]), 13));
+    double ar = 0.0, ab = 0.0;
 #pragma unroll
     for (int i = 1; i < 9; ++i) {
         uint16_t q, u;
-        float N, nr;
-        enc_pair<ST>(S, vclass(i), P.n[i], t[i], weyl(seed, i), CG_CODEC_SR != 0, q, u, N, nr);
-        sn = i == 1 ? (double)N : sn + (double)N;
-        sr = i == 1 ? (double)nr : sr + (double)nr;
-        C::put(q, h.r[0], at.col, plane_off<ST>(i) + at.row);
-        C::put(u, h.r[1], at.col, plane_off<ST>(i) + at.row);
+        float nr, nb;
+        enc_pair<ST>(S, vclass(i), outr[i], outb[i], weyl(seed, 2 * i), weyl(seed, 2 * i + 1), CG_CODEC_SR != 0, q, u, nr,
+                     nb);
+        ar += (double)nr;
+        ab += (double)nb;
+        put(i, q, u);
     }
-    store_rest(S, h, at, mr - sr, mb - (sn - sr), seed);
+    const uint32_t r1 = weyl(seed, 18), r2 = weyl(seed, 19);
+    const double d1 = CG_CODEC_SR ? (double)(r1 >> 8) * 0x1p-24 : 0.5, d2 = CG_CODEC_SR ? (double)(r2 >> 8) * 0x1p-24 : 0.5;
+    rest(0, enc_rest(mr - ar, S.rest0[0], d1));
+    rest(1, enc_rest(mb - ab, S.rest0[1], d2));
+}
+
+// The same to a population buffer.
+template <int ST>
+__device__ __forceinline__ void store_16_node(const SlotDesc &S, const Halves &h, const NodeAt &at, const float *outr,
+                                              const float *outb, double mr, double mb)
+{
+    using C = Codec<ST>;
+    put_16_node<ST>(
+        S, at.pos, outr, outb, mr, mb,
+        [&](int i, uint16_t q, uint16_t u) {
+            C::put(q, h.r[0], at.col, plane_off<ST>(i) + at.row);
+            C::put(u, h.r[1], at.col, plane_off<ST>(i) + at.row);
+        },
+        [&](int k, uint32_t bits) {
+            __builtin_amdgcn_raw_buffer_store_b32(bits, h.r[k], (int)at.rcol, (int)at.row, CG_STORE_POLICY);
+        });
+}
+
+// A row's 18 stores, dropped (see step_body): stands in for the stores of a row
+// on the way into a loop or through it where nothing is written.
+template <int ST, int POL = CG_STORE_POLICY>
+__device__ __forceinline__ void store_nothing(const Halves &h)
+{
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            if (rest32<ST>() && i > 0)
+                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)0, h.r[k], (int)kNoStore, (int)plane_off<ST>(i), POL);
+            else __builtin_amdgcn_raw_buffer_store_b32(0u, h.r[k], (int)kNoStore, (int)plane_off<ST>(i), POL);
+        }
 }
 
 }  // namespace cgd

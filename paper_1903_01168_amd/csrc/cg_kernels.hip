@@ -11,6 +11,8 @@
 //              layout and a workgroup's wavefronts trade edge columns
 //              through LDS, one barrier per row; whole cache lines written,
 //              for lattices beyond the cache).
+//  k_step_two  two fused time steps in FP32 storage, the state between them in
+//              LDS (lattices that keep the chip full).
 //  k_init      equilibrium initialisation from FP32 fields.
 //  k_moments   fields at the current step (+ FP64 per-block diagnostics).
 //  k_reduce    fixed-order FP64 reduction of the per-block partials.
@@ -88,9 +90,14 @@ template <int ST, bool NSC, int POL = CG_STORE_POLICY>
 __device__ __forceinline__ void collide_store(const SlotDesc &S, const Halves &dst, const NodeAt &at, const Node &cur,
                                               float psi, float Fx, float Fy, bool nsc, float dqx, float dqy)
 {
-    const Post P = collide<NSC>(S, cur, psi, Fx, Fy, nsc, dqx, dqy);
-    if constexpr (ST == ST_F32) store_f32_node<POL>(dst, at, P, cur.mr, cur.mb);
-    else store_16_node<ST>(S, dst, at, P, cur.mr, cur.mb);
+    if constexpr (ST == ST_F32) {
+        const Post P = collide<NSC>(S, cur, psi, Fx, Fy, nsc, dqx, dqy);
+        store_f32_node<POL>(dst, at, P, cur.mr, cur.mb);
+    } else {
+        Keep18 k;
+        collide_16<NSC>(S, cur, psi, Fx, Fy, k, nsc, dqx, dqy);
+        store_16_node<ST>(S, dst, at, k.r, k.b, cur.mr, cur.mb);
+    }
 }
 
 // Colour field of one row as Psi3, and the halo nodes' values (lanes 0, 1,
@@ -169,6 +176,8 @@ __device__ __forceinline__ void step_nn(const SlotDesc *__restrict__ slots, int 
     const XCols xc = make_cols<ST>(S, xg);
     const Halves src = halves<ST>(S, parity ? S.buf[1] : S.buf[0]);
     const Halves dst = halves<ST>(S, parity ? S.buf[0] : S.buf[1]);
+
+    constexpr bool kMasked = ST == ST_F32;     // see step_body
 
     // halo nodes of the workgroup (x0-1, x0-2, x1+1, x1), gathered by
     // wavefront 0: the packed gather's source column of this lane; the
@@ -293,7 +302,7 @@ __device__ __forceinline__ void step_nn(const SlotDesc *__restrict__ slots, int 
         Own o{};
         if (active) {
             o.nd = finish<ST>(S, p.m, xc, rw);
-            o.c = color_field(S, o.nd.rr(), o.nd.rb());
+            o.c = color_field<ST>(S, o.nd.rr(), o.nd.rb());
             if (nsc) qnode(o.nd, o.qx, o.qy);
         }
         if (halo_wave) {
@@ -304,7 +313,7 @@ __device__ __forceinline__ void step_nn(const SlotDesc *__restrict__ slots, int 
                 hxc.outlet = hxg == nx - 1;
             }
             const Node hn = finish<ST>(S, halo_raw<ST>(p.h, lane), hxc, rw);
-            o.hc = color_field(S, hn.rr(), hn.rb());
+            o.hc = color_field<ST>(S, hn.rr(), hn.rb());
             if (nsc) qnode(hn, o.hqx, o.hqy);
         }
         return o;
@@ -387,6 +396,7 @@ __device__ __forceinline__ void step_nn(const SlotDesc *__restrict__ slots, int 
     RowSrc rwp = make_row<ST>(S, have_p ? real_row(ys + d) : ys, inlet_wave);
     Pend pend;
     if (have_p) pend = issue_row(rwp);
+    if constexpr (kMasked) store_nothing<ST, kXchStorePolicy>(dst);
 
     const float fd = (float)d;
     for (int y = ys; y != ye; y += d) {
@@ -414,11 +424,11 @@ __device__ __forceinline__ void step_nn(const SlotDesc *__restrict__ slots, int 
             pa = ghost(p0);                     // row y+d lies beyond a wall
             if (nsc) qa = qghost(cur, q0);
         }
-        if (out_lane) {
+        if (kMasked || out_lane) {   // see step_body
             float Fx, Fy;
             gradient(pb, p0, pa, fd, Fx, Fy);
             if ((S.flags & F_WET) && (y == 0 || y == ny - 1)) wet(S, y == 0, Fx, Fy);
-            const NodeAt at{xc.o0, xc.r0, (uint32_t)y * (uint32_t)S.row_bytes,
+            const NodeAt at{kMasked && !out_lane ? kNoStore : xc.o0, xc.r0, (uint32_t)y * (uint32_t)S.row_bytes,
                             2u * ((uint32_t)y * (uint32_t)S.pitch + (uint32_t)xg)};
             float dqx = 0.f, dqy = 0.f;
             if constexpr (NSC) {
@@ -473,6 +483,16 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
     const int xg = xper ? wrapi(xl, nx) : (xl < 0 ? 0 : (xl >= nx ? nx - 1 : xl));
     const bool out_lane = lane >= kHalo && lane < 64 - kHalo && xl < nx;
     const XCols xc = make_cols<ST>(S, xg);
+    // FP32: every lane computes and stores; halo lanes carry an offset beyond
+    // the buffer, so that the hardware drops their stores.  A branch around the
+    // stores (and a loop entered without any) would leave the compiler unable
+    // to tell how many stores are younger than the row's loads: it then waits
+    // for all of them to complete, every row, before it uses what was loaded.
+    // (16-bit storage keeps the branch: its collision is contracted by the
+    // compiler, and where the block of code begins is part of how it rounds,
+    // hence of the dither, see collide_16.)
+    constexpr bool kMasked = ST == ST_F32;
+    const uint32_t col_out = kMasked && !out_lane ? kNoStore : xc.o0;
     const Halves src = halves<ST>(S, parity ? S.buf[1] : S.buf[0]);
     const Halves dst = halves<ST>(S, parity ? S.buf[0] : S.buf[1]);
 
@@ -587,11 +607,11 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
             const Raw18<ST> r0 = issue<ST>(S, src, xc, w0);
             if (ha1) ra1 = issue<ST>(S, src, xc, wa1);
             cur = finish<ST>(S, r0, xc, w0);
-            c0 = color_field(S, cur.rr(), cur.rb());
+            c0 = color_field<ST>(S, cur.rr(), cur.rb());
             if (nsc) q0 = qreal(cur);
             if (hb1) {
                 const Node t = finish<ST>(S, rb1, xc, wb1);
-                cb1 = color_field(S, t.rr(), t.rb());
+                cb1 = color_field<ST>(S, t.rr(), t.rb());
                 if (nsc) qb = qreal(t);
             } else {
                 cb1 = ghost1(c0);
@@ -599,13 +619,13 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
             }
             if (hb2) {
                 const Node t = finish<ST>(S, rb2, xc, wb2);
-                cb2 = color_field(S, t.rr(), t.rb());
+                cb2 = color_field<ST>(S, t.rr(), t.rb());
             } else {
                 cb2 = hb1 ? ghost1(cb1) : cb1;   // beyond a wall: distance 1, or the inner ghost row
             }
             if (ha1) {
                 nxt = finish<ST>(S, ra1, xc, wa1);
-                ca1 = color_field(S, nxt.rr(), nxt.rb());
+                ca1 = color_field<ST>(S, nxt.rr(), nxt.rb());
                 if (nsc) qa = qreal(nxt);
             } else {
                 ca1 = ghost1(c0);
@@ -616,6 +636,7 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
         Raw18<ST> pend;
         RowSrc wp = make_row<ST>(S, hp ? real_row(ys + 2 * d) : ys, inlet_wave);
         if (hp) pend = issue<ST>(S, src, xc, wp);
+        if constexpr (kMasked) store_nothing<ST>(dst);
 
         const float fd = (float)d;
         for (int y = ys; y != ye; y += d) {
@@ -624,7 +645,7 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
             QRow q2{};
             if (hp) {
                 nn = finish<ST>(S, pend, xc, wp);
-                ca2 = color_field(S, nn.rr(), nn.rb());
+                ca2 = color_field<ST>(S, nn.rr(), nn.rb());
                 if (nsc) q2 = qreal(nn);
             } else if (gathered(y + d)) {       // row y+2d is the ghost row next to a wall
                 ca2 = ghost1(ca1);
@@ -638,7 +659,7 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
                 pend = issue<ST>(S, src, xc, wp);
             }
             const Psi5 pb2 = psi5(cb2), pb1 = psi5(cb1), p0 = psi5(c0), pa1 = psi5(ca1), pa2 = psi5(ca2);
-            if (out_lane) {
+            if (kMasked || out_lane) {
                 // F_x = sum over rows dy of w(1+dy^2) (psi(+1) - psi(-1)) + 2 w(4+dy^2) (psi(+2) - psi(-2));
                 // F_y = sum over rows of dy [w(dy^2) psi(0) + w(1+dy^2) (psi(+1) + psi(-1))
                 //                            + w(4+dy^2) (psi(+2) + psi(-2))]
@@ -650,7 +671,7 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
                                  2.f * ((1.f / 60.f) * (pa2.c - pb2.c) + (2.f / 315.f) * (sx1(pa2) - sx1(pb2)) +
                                         (1.f / 5040.f) * (sx2(pa2) - sx2(pb2))));
                 if ((S.flags & F_WET) && (y == 0 || y == ny - 1)) wet(S, y == 0, Fx, Fy);
-                const NodeAt at{xc.o0, xc.r0, (uint32_t)y * (uint32_t)S.row_bytes,
+                const NodeAt at{col_out, xc.r0, (uint32_t)y * (uint32_t)S.row_bytes,
                                 2u * ((uint32_t)y * (uint32_t)S.pitch + (uint32_t)xg)};
                 float dqx = 0.f, dqy = 0.f;
                 if constexpr (NSC) {
@@ -691,17 +712,19 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
         if (have_p) pend = issue<ST>(S, src, xc, rwp);
         if (have_b) {
             const Node t = finish<ST>(S, rb, xc, rwb);
-            pb = psi3(color_field(S, t.rr(), t.rb()));
+            pb = psi3(color_field<ST>(S, t.rr(), t.rb()));
             if (nsc) qb = qreal(t);
         }
         cur = finish<ST>(S, r0, xc, rw0);
-        p0 = psi3(color_field(S, cur.rr(), cur.rb()));
+        p0 = psi3(color_field<ST>(S, cur.rr(), cur.rb()));
         if (nsc) q0 = qreal(cur);
         if (!have_b) {                         // the row behind lies beyond a wall
             pb = ghost(p0);
             if (nsc) qb = qghost(cur);
         }
     }
+
+    if constexpr (kMasked) store_nothing<ST>(dst);
 
     const float fd = (float)d;
     for (int y = ys; y != ye; y += d) {
@@ -710,7 +733,7 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
         QRow qa{};
         if (have_p) {
             nxt = finish<ST>(S, pend, xc, rwp);
-            pa = psi3(color_field(S, nxt.rr(), nxt.rb()));
+            pa = psi3(color_field<ST>(S, nxt.rr(), nxt.rb()));
             if (nsc) qa = qreal(nxt);
         } else {
             pa = ghost(p0);                    // row y+d lies beyond a wall
@@ -723,11 +746,11 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
             rwp = make_row<ST>(S, real_row(r2), inlet_wave);
             pend = issue<ST>(S, src, xc, rwp);
         }
-        if (out_lane) {
+        if (kMasked || out_lane) {
             float Fx, Fy;
             gradient(pb, p0, pa, fd, Fx, Fy);
             if ((S.flags & F_WET) && (y == 0 || y == ny - 1)) wet(S, y == 0, Fx, Fy);
-            const NodeAt at{xc.o0, xc.r0, (uint32_t)y * (uint32_t)S.row_bytes,
+            const NodeAt at{col_out, xc.r0, (uint32_t)y * (uint32_t)S.row_bytes,
                             2u * ((uint32_t)y * (uint32_t)S.pitch + (uint32_t)xg)};
             float dqx = 0.f, dqy = 0.f;
             if constexpr (NSC) {
@@ -741,6 +764,284 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
         qb = q0;
         q0 = qa;
         cur = nxt;
+    }
+}
+
+// Two fused time steps, halo lanes: a wavefront marches along a strip of rows
+// on its own, as in step_body, and carries two steps along: it collides row a
+// of the first step, whose populations go to a ring of rows in LDS, pulls row
+// b = a - d of the second step from the ring, and collides and stores row
+// c = b - d of the second step.  The populations are read from and written to
+// memory once for two steps.  Strips overlap by three rows on either side,
+// wavefronts by 2 h columns (two_halo).  FP32 storage: the 16-bit formats'
+// steps are bound by the codec's arithmetic, and collisions done twice there
+// cost more than the traffic saved (8192 x 512 channel 104 -> 171 us a step).
+//
+// Measured, us per step, exchange step before against this: the 8192 x 512
+// channel 125 -> 91, 4096 x 2048 240 -> 170.  Two steps of the channel move
+// 410 MB in and 319 MB out (a single one 302 each way at least); what bounds
+// it now is the instruction rate of its 4 wavefronts per SIMD: 579 vector
+// instructions per 64-lane row and two steps, issued in 54% of the cycles,
+// the waits for LDS and memory in between.
+//
+// The ring (this wavefront's own; LDS operations of a wavefront complete in
+// order, so fences only keep the compiler from reordering them) holds of each
+// row what later rows still pull from it: the populations moving along the
+// march (c_y = d) of three rows, those staying in their row (c_y = 0) of two,
+// those moving against the march of one.  Rows beyond a wall are written to
+// the ring as the populations that the wall sends back.
+//
+// Everything a node's arithmetic consists of (finish, collide) is the code of
+// the single step, uncontracted or with explicit fused multiply-adds, so two
+// steps give the bits of two single ones.
+template <int W>
+__device__ __forceinline__ void step_two(const SlotDesc *__restrict__ slots, int nslots, int total_tiles, int parity)
+{
+    constexpr int ST = ST_F32;
+    constexpr int kSet = 6;                          // words of the populations of one c_y
+    constexpr int kWords = 6 * kSet;                 // 3 rows along, 2 staying, 1 against
+    __shared__ uint32_t ring[W * kWords * 64 + 2];
+
+    const int tile = xcd_tile(blockIdx.x, total_tiles);
+    const SlotDesc &S = slots[find_slot(slots, nslots, tile)];
+    const int lt = tile - S.tile_begin;
+    const int tyi = lt / S.tiles_x;
+    const int txi = lt - tyi * S.tiles_x;
+    const int nx = S.nx, ny = S.ny;
+    const int lane = threadIdx.x & 63;
+    const int wave = (int)(threadIdx.x >> 6);
+    const bool yper = S.flags & F_YPER;
+    const bool xper = S.flags & F_XPER;
+    const int y0 = tyi * S.strip;
+    const int y1 = min(y0 + S.strip, ny);
+    // strips whose first step has no wall row take the narrower halo; the last
+    // wavefronts of their rows are then left without a column
+    const int hl = two_halo(yper || (y0 >= 3 && y1 <= ny - 3));
+    const int xw = (txi * W + wave) * (64 - 2 * hl);
+    if (xw >= nx) return;                      // uniform per wavefront (no barriers below)
+    const bool inlet_wave = xw == 0;
+
+    const int xl = xw - hl + lane;             // the lane's column (may lie outside the lattice)
+    const int xg = map_col(S, xl);
+    const bool out_lane = lane >= hl && lane < 64 - hl && xl < nx;
+    const XCols xc = make_cols<ST>(S, xg);
+    const Halves src = halves<ST>(S, parity ? S.buf[1] : S.buf[0]);
+    const Halves dst = halves<ST>(S, parity ? S.buf[0] : S.buf[1]);
+
+    // wall ghost row of the colour field (see step_body); its weights are
+    // formed here, at wall rows only
+    auto ghost = [&](float c) -> float {
+        const float w = from_west(c), e = from_east(c);
+        const int x = opaque(xl);
+        const bool in0 = xper || (x >= 0 && x < nx);
+        const bool inw = xper || (x - 1 >= 0 && x - 1 < nx);
+        const bool ine = xper || (x + 1 >= 0 && x + 1 < nx);
+        const float gden = (in0 ? 4.f : 0.f) + (inw ? 1.f : 0.f) + (ine ? 1.f : 0.f);
+        const float ginv = gden > 0.f ? fast_rcp(gden) : 0.f;
+        return ((in0 ? 4.f * c : 0.f) + (inw ? w : 0.f) + (ine ? e : 0.f)) * ginv;
+    };
+    auto real_row = [&](int r) { return yper ? wrap_near(r, ny) : r; };
+    auto gathered = [&](int r) { return yper || (r >= 0 && r < ny); };
+
+    const int d = (tyi & 1) ? -1 : 1;          // even strips march up, odd ones down (see step_body)
+    const float fd = (float)d;
+    const int ys = d > 0 ? y0 : y1 - 1;        // first row written
+    const int yl = d > 0 ? y1 - 1 : y0;        // last row written
+    // first and last row of the first step (a wall ends its rows earlier)
+    const int a0 = yper ? ys - 2 * d : (d > 0 ? max(ys - 2, 0) : min(ys + 2, ny - 1));
+    const int a1 = yl + 2 * d;
+
+    // --- ring ---
+    // A word is 64 lanes' values.  Lanes 0 and 63 reach one lane beyond their
+    // word, into a neighbouring one (or the word before or after the array):
+    // neither they nor what they read or write there is ever used.
+    const int own = 1 + wave * (kWords * 64) + lane;
+    auto fence = [&]() {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    // word offset of a row's populations with c_y = s: rows are counted along
+    // the march, k = 0, 1, 2 the ring slots of the row and of the ones behind
+    int along[3] = {0, kSet * 64, 2 * kSet * 64};    // slots of rows a, a-d, a-2d
+    int stay[2] = {3 * kSet * 64, 4 * kSet * 64};    // slots of rows a, a-d
+    constexpr int against = 5 * kSet * 64;           // row a
+    auto jx = [](int i) { return cx(i) == 0 ? 0 : (cx(i) > 0 ? 1 : 2); };
+    // word of population i (colour half k) inside its set
+    auto word = [&](int i, int k) { return 2 * jx(i) + k; };
+    auto set_off = [&](int i, int up, int mid, int down) { return cy(i) > 0 ? up : (cy(i) < 0 ? down : mid); };
+    // collide a node of row a and put what leaves it
+    auto put_row = [&](const Node &nd, float psi, float Fx, float Fy) {
+        const int up = d > 0 ? along[0] : against, down = d > 0 ? against : along[0];
+        put_f32_node(collide(S, nd, psi, Fx, Fy), nd.mr, nd.mb, [&](int i, int k, float v) {
+            ring[set_off(i, up, stay[0], down) + word(i, k) * 64 + own] = __float_as_uint(v);
+        });
+    };
+    // the pulled populations of row b = a - d
+    auto pull_row = [&]() -> Raw18<ST> {
+        const int up = d > 0 ? along[2] : against, down = d > 0 ? against : along[2];
+        Raw18<ST> r;
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            const int o = set_off(i, up, stay[1], down);
+            r.v[i] = ring[o + word(i, 0) * 64 + own - cx(i)];
+            r.v[9 + i] = ring[o + word(i, 1) * 64 + own - cx(i)];
+        }
+        return r;
+    };
+    // What a wall sends back into its row: the set `to` (of the row beyond the
+    // wall, moving into the lattice) from the set `from` of the wall row,
+    // moving into the wall: the node's own opposite population (no slip; left
+    // where the pull of that node finds it) or the mirrored one (free slip)
+    auto wall_row = [&](int from, int to, bool slip) {
+        constexpr int n = kSet / 3;              // words per direction
+#pragma unroll
+        for (int k = 0; k < n; ++k) {
+            const uint32_t v0 = ring[from + k * 64 + own];            // c_x = 0
+            const uint32_t vp = ring[from + (n + k) * 64 + own];      // c_x = +1
+            const uint32_t vm = ring[from + (2 * n + k) * 64 + own];  // c_x = -1
+            ring[to + k * 64 + own] = v0;
+            ring[to + (n + k) * 64 + own - (slip ? 0 : 1)] = slip ? vp : vm;
+            ring[to + (2 * n + k) * 64 + own + (slip ? 0 : 1)] = slip ? vm : vp;
+        }
+    };
+    auto slip_at = [&](int y) { return (bool)(S.flags & (y == 0 ? F_SLIP_LO : F_SLIP_HI)); };
+
+    // --- first step: prologue as in step_body, at row a0 ---
+    bool have_p = gathered(a0 + d);
+    RowSrc rwp = make_row<ST>(S, have_p ? real_row(a0 + d) : a0, inlet_wave);
+    Raw18<ST> pend;
+    // colour field of rows a-d and a (values only: their neighbours' sums and
+    // differences are formed where they are used, which saves registers)
+    float pb, p0;
+    Node cur;                                  // row a
+    {
+        const bool have_b = gathered(a0 - d);
+        Raw18<ST> rb;
+        const RowSrc rwb = make_row<ST>(S, have_b ? real_row(a0 - d) : a0, inlet_wave);
+        if (have_b) rb = issue<ST>(S, src, xc, rwb);
+        const RowSrc rw0 = make_row<ST>(S, real_row(a0), inlet_wave);
+        const Raw18<ST> r0 = issue<ST>(S, src, xc, rw0);
+        if (have_p) pend = issue<ST>(S, src, xc, rwp);
+        if (have_b) {
+            const Node t = finish<ST>(S, rb, xc, rwb);
+            pb = color_field<ST>(S, t.rr(), t.rb());
+        }
+        cur = finish<ST>(S, r0, xc, rw0);
+        p0 = color_field<ST>(S, cur.rr(), cur.rb());
+        if (!have_b) pb = ghost(p0);
+    }
+    // second step: colour field of rows c-d and c, node of row c
+    float qb = 0.f, q0 = 0.f;
+    Node cur2{};
+    // an open face's waves: the lane that holds the nearest column of the lattice
+    const bool face = !xper && (xw - hl < 0 || xw - hl + 63 >= nx);
+
+    // Wavefronts that are behind go first: the older ones of a SIMD would
+    // otherwise be served first throughout and end long before the others,
+    // whose last rows then leave the SIMD half idle.
+    const int rows = (a1 - a0) * d, quarter = rows >> 2;
+    int left = rows;
+    __builtin_amdgcn_s_setprio(3);
+    // rb: rows from the strip's first row to row b along the march
+    const int last = (yl - ys) * d + 1;
+    int a = a0, rb = (a0 - ys) * d - 1;
+    float qa = 0.f;                            // second step: colour field and node of row b
+    Node n2{};
+    bool row_b = false;
+    // row a of the first step and row b of the second one's nodes
+    auto front = [&]() {
+        if (left == rows - quarter) __builtin_amdgcn_s_setprio(2);
+        else if (left == rows - 2 * quarter) __builtin_amdgcn_s_setprio(1);
+        else if (left == rows - 3 * quarter) __builtin_amdgcn_s_setprio(0);
+        if (gathered(a)) {
+            Node nxt;
+            float pa;
+            if (have_p) {
+                nxt = finish<ST>(S, pend, xc, rwp);
+                pa = color_field<ST>(S, nxt.rr(), nxt.rb());
+            } else {
+                pa = ghost(p0);
+            }
+            const int ya = real_row(a);
+            float Fx, Fy;
+            gradient(psi3(pb), psi3(p0), psi3(pa), fd, Fx, Fy);
+            if ((S.flags & F_WET) && (ya == 0 || ya == ny - 1)) wet(S, ya == 0, Fx, Fy);
+            put_row(cur, p0, Fx, Fy);
+            fence();
+            // request row a+2d now; it arrives while the second step's row is
+            // formed and collides (requested earlier it would hold 18 more
+            // registers through the collision above)
+            const int r2 = a + 2 * d;
+            have_p = (d > 0 ? r2 <= a1 + 1 : r2 >= a1 - 1) && gathered(r2);
+            if (have_p) {
+                rwp = make_row<ST>(S, real_row(r2), inlet_wave);
+                pend = issue<ST>(S, src, xc, rwp);
+            }
+            if (!gathered(a - d)) wall_row(against, along[1], slip_at(a));   // the wall behind
+            pb = p0;
+            p0 = pa;
+            cur = nxt;
+        } else if (gathered(a - d)) {
+            wall_row(along[1], against, slip_at(a - d));                     // the wall ahead
+        }
+        fence();
+        // row b = a - d of the second step: its node and colour field; b = ys - d
+        // beyond a wall behind is formed with row ys
+        const int b = a - d;
+        const bool real_b = gathered(b);
+        row_b = rb >= (real_b ? -1 : 0);
+        qa = 0.f;
+        if (row_b) {
+            if (real_b) {
+                RowSrc rw;
+                rw.icol = (inlet_wave && (S.flags & F_XOPEN))
+                              ? (int)((const __attribute__((address_space(1))) int8_t *)S.inlet_color)[real_row(b)]
+                              : 0;
+                n2 = finish<ST>(S, pull_row(), xc, rw);
+                qa = color_field<ST>(S, n2.rr(), n2.rb());
+                if (face) qa = __shfl(qa, map_col(S, opaque(xl)) - (xw - hl), 64);
+                if (!gathered(b - d)) q0 = ghost(qa);
+            } else {
+                qa = ghost(q0);
+            }
+        }
+    };
+    auto next = [&]() {
+        if (row_b) {
+            qb = q0;
+            q0 = qa;
+            cur2 = n2;
+        }
+        fence();
+        // row a+d takes the oldest slots
+        const int t = along[2];
+        along[2] = along[1];
+        along[1] = along[0];
+        along[0] = t;
+        const int u = stay[1];
+        stay[1] = stay[0];
+        stay[0] = u;
+        a += d;
+        --left;
+        ++rb;
+    };
+    // until row c = b - d is the strip's first one (a loop of its own, so that
+    // the rows of the other one always store, see step_body)
+    while (rb <= 0) {
+        front();
+        next();
+    }
+    store_nothing<ST>(dst);
+    for (;; next()) {
+        front();
+        const int c = a - 2 * d;
+        float Fx, Fy;
+        gradient(psi3(qb), psi3(q0), psi3(qa), fd, Fx, Fy);
+        if ((S.flags & F_WET) && (c == 0 || c == ny - 1)) wet(S, c == 0, Fx, Fy);
+        const NodeAt at{out_lane ? xc.o0 : kNoStore, out_lane ? xc.r0 : kNoStore, (uint32_t)c * (uint32_t)S.row_bytes,
+                        2u * ((uint32_t)c * (uint32_t)S.pitch + (uint32_t)xg)};
+        collide_store<ST, false>(S, dst, at, cur2, q0, Fx, Fy, false, 0.f, 0.f);
+        if (rb == last) break;
     }
 }
 
@@ -763,6 +1064,13 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 
 k_step(const SlotDesc *__restrict__ slots, int nslots, int total_tiles, int parity, int launch_idx)
 {
     step_any<ST, W, KV>(slots, nslots, total_tiles, parity, launch_idx);
+}
+
+template <int W>
+__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 8)))
+k_step_two(const SlotDesc *__restrict__ slots, int nslots, int total_tiles, int parity)
+{
+    step_two<W>(slots, nslots, total_tiles, parity);
 }
 
 template <int ST, int W, int KV>
@@ -798,7 +1106,9 @@ __global__ void __launch_bounds__(256) k_init(const SlotDesc *__restrict__ sd, c
                 e[k][i] = rk[k] * (S.phi[k][vclass(i)] + wgt(i) * (lin + 4.5f * cu * cu - 1.5f * uu));
                 if (i == 0) e[k][i] += rk[k] * S.phi0_eps[k];
             }
-        store18<ST>(S, dst, node_at<ST>(S, x, y), e[0], e[1], (double)rk[0], (double)rk[1]);
+        const NodeAt at = node_at<ST>(S, x, y);
+        if constexpr (ST == ST_F32) store18_nearest<ST>(S, dst, at, e[0], e[1]);
+        else store_16_node<ST>(S, dst, at, e[0], e[1], (double)rk[0], (double)rk[1]);
     }
 }
 
@@ -840,7 +1150,7 @@ __global__ void __launch_bounds__(256) k_moments(const SlotDesc *__restrict__ sd
         }
         acc[0] += (double)nd.rr();
         acc[1] += (double)nd.rb();
-        acc[2] += 0.5 * (1.0 + (double)color_field(S, nd.rr(), nd.rb()));
+        acc[2] += 0.5 * (1.0 + (double)color_field<ST>(S, nd.rr(), nd.rb()));
         const double um = sqrt((double)ux * ux + (double)uy * uy);
         acc[8] = um > acc[8] ? um : acc[8];
         if (r_in > 0.0 || r_out > 0.0) {
@@ -984,6 +1294,17 @@ static hipError_t step_v(int tx, const SlotDesc *d, int nslots, int tiles, int p
     return hipGetLastError();
 }
 
+static hipError_t step_two_tx(int tx, const SlotDesc *d, int nslots, int tiles, int parity, hipStream_t s)
+{
+    switch (tx) {
+    case 64: hipLaunchKernelGGL((k_step_two<1>), dim3(tiles), dim3(64), 0, s, d, nslots, tiles, parity); break;
+    case 128: hipLaunchKernelGGL((k_step_two<2>), dim3(tiles), dim3(128), 0, s, d, nslots, tiles, parity); break;
+    case 256: hipLaunchKernelGGL((k_step_two<4>), dim3(tiles), dim3(256), 0, s, d, nslots, tiles, parity); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 template <int ST>
 static hipError_t step_st(int tx, const SlotDesc *d, int nslots, int tiles, int parity, int idx, hipStream_t s,
                           int variant)
@@ -995,6 +1316,7 @@ static hipError_t step_st(int tx, const SlotDesc *d, int nslots, int tiles, int 
     case KV_NSC | KV_ISO: return step_v<ST, KV_NSC | KV_ISO>(tx, d, nslots, tiles, parity, idx, s);
     case KV_XCH: return step_v<ST, KV_XCH>(tx, d, nslots, tiles, parity, idx, s);
     case KV_XCH | KV_NSC: return step_v<ST, KV_XCH | KV_NSC>(tx, d, nslots, tiles, parity, idx, s);
+    case KV_TWO: return ST == ST_F32 ? step_two_tx(tx, d, nslots, tiles, parity, s) : hipErrorInvalidValue;
     }
     return hipErrorInvalidValue;
 }

@@ -13,7 +13,9 @@ namespace cgd {
 // whole 64-column blocks and take their edge columns from each other through
 // LDS (full-line stores, for lattices beyond the cache), instead of holding
 // halo columns in their own outer lanes.  Both give the same bits.
-enum : int { KV_NSC = 1, KV_ISO = 2, KV_XCH = 4 };
+// KV_TWO (FP32 storage, nearest-neighbour gradient, no correction) is a
+// launch choice as well: one launch advances two steps, the state between them in LDS.
+enum : int { KV_NSC = 1, KV_ISO = 2, KV_XCH = 4, KV_TWO = 8 };
 // The variant a lattice needs alone.
 inline int step_variant(const SlotDesc &d)
 {
