@@ -324,6 +324,34 @@ int plan_two_strip(const lbm_params *p, long long nodes, long long wave_rows, in
     return std::min(s, p->ny);
 }
 
+static void tile_grid(const lbm_params *p, int T, int &tx, int &ty)
+{
+    const int cols = cgd::tile_cols(T, p->bc_ylo == LBM_BC_PERIODIC), rows = cgd::tile_out(T);
+    tx = (p->nx + cols - 1) / cols;
+    ty = (p->ny + rows - 1) / rows;
+}
+
+// Two or three steps per launch, one row per wavefront.  A workgroup takes a
+// CU, so a launch takes whole rounds of 256 of them, whatever they hold: 2.0 +
+// 10 us for three steps in one round, 2.0 + 8 us for two (us per step, one
+// step a launch against three and two: 64^2 4.9 / 3.7 / 4.5, 200^2 5.8 / 3.9,
+// 300 x 200 6.8 / 4.05 / 5.1, 320^2 8.4 / 7.1 in two rounds / 5.2 in one;
+// with walls, wetting and correction 64^2 5.3 / 4.0, 300 x 200 7.2 / 4.3, 400
+// x 300 8.7 / 7.8 / 5.7).  Two rounds of two steps pay from 180 000 nodes (400
+// x 400 9.26 / 9.26, 512 x 400 9.9 / 9.3, 512^2 11.6 / 9.5, with correction
+// and walls 1024 x 256 12.4 / 10.2), three do not (512^2 between walls 12.4 /
+// 13.9, 600^2 13.8 / 13.3, 700 x 640 15.7 / 17.1).
+int plan_tile(const lbm_params *p, int variant)
+{
+    if (p->storage != LBM_STORE_F32 || (variant & cgd::KV_ISO) || p->ny < 4) return 0;
+    int tx, ty;
+    tile_grid(p, 3, tx, ty);
+    if ((long long)tx * ty <= 256) return 3;
+    tile_grid(p, 2, tx, ty);
+    if ((long long)tx * ty <= 256) return 2;
+    return (long long)tx * ty <= 512 && (long long)p->nx * p->ny >= 180000 ? 2 : 0;
+}
+
 void set_geometry(SlotDesc &d, const lbm_params *p, const Layout &L, int tx, int strip, bool xch, bool two)
 {
     d.nx = p->nx;
@@ -391,15 +419,23 @@ static int replan(lbm_ctx *c)
     c->tiles = c->desc.tiles_x * c->desc.tiles_y;
     c->tx = tx;
     const long long nodes = (long long)c->p.nx * c->p.ny;
-    c->two = c->xch_req < 0 && plan_two(nodes, c->p.storage, var, c->p.ny);
+    c->fused = 1;
     c->desc2 = c->desc;
-    if (c->two) {
+    const int T = c->xch_req < 0 && !c->tx_req && !c->strip_req ? plan_tile(&c->p, var) : 0;
+    if (T) {
+        c->fused = T;
+        c->fused_kv = cgd::KV_TILE | (T == 2 ? cgd::KV_TWO : 0) | var;
+        c->tx2 = 64 * cgd::kTileRows;
+        c->desc2.strip = cgd::tile_out(T);
+        tile_grid(&c->p, T, c->desc2.tiles_x, c->desc2.tiles_y);
+    } else if (c->xch_req < 0 && plan_two(nodes, c->p.storage, var, c->p.ny)) {
+        c->fused = 2;
+        c->fused_kv = cgd::KV_TWO;
         c->tx2 = two_tx(c->p.nx, c->tx_req);
         set_geometry(c->desc2, &c->p, c->lay, c->tx2,
-                     plan_two_strip(&c->p, nodes, (long long)two_waves(&c->p) * c->p.ny, c->strip_req), false,
-                     true);
-        c->tiles2 = c->desc2.tiles_x * c->desc2.tiles_y;
+                     plan_two_strip(&c->p, nodes, (long long)two_waves(&c->p) * c->p.ny, c->strip_req), false, true);
     }
+    c->tiles2 = c->desc2.tiles_x * c->desc2.tiles_y;
     drop_graphs(c);
     return upload_desc(c);
 }
@@ -591,11 +627,14 @@ static const int kGraphSteps = 32;   // steps per captured graph (a multiple of 
 
 static int ctx_variant(const lbm_ctx *c) { return cgd::step_variant(c->desc) | (c->xch ? cgd::KV_XCH : 0); }
 
-// One launch at parity `par` on stream s: two steps, or one
-static hipError_t ctx_launch(lbm_ctx *c, bool two, int par, hipStream_t s)
+// The same of this lattice: an even number of whole launches
+static int graph_steps(const lbm_ctx *c) { return kGraphSteps / (2 * c->fused) * (2 * c->fused); }
+
+// One launch at parity `par` on stream s: c->fused steps, or one
+static hipError_t ctx_launch(lbm_ctx *c, bool fused, int par, hipStream_t s)
 {
-    if (two) return cgd::launch_step(c->p.storage, c->tx2, c->d_desc + 1, 1, c->tiles2, par, 0, s, cgd::KV_TWO);
-    return cgd::launch_step(c->p.storage, c->tx, c->d_desc, 1, c->tiles, par, 0, s, ctx_variant(c));
+    if (!fused) return cgd::launch_step(c->p.storage, c->tx, c->d_desc, 1, c->tiles, par, 0, s, ctx_variant(c));
+    return cgd::launch_step(c->p.storage, c->tx2, c->d_desc + 1, 1, c->tiles2, par, 0, s, c->fused_kv);
 }
 
 static int build_graph(lbm_ctx *c, int parity)
@@ -604,8 +643,8 @@ static int build_graph(lbm_ctx *c, int parity)
     hipError_t e = hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(c, e, "hipStreamBeginCapture");
     hipError_t le = hipSuccess;
-    for (int j = 0; j < (c->two ? kGraphSteps / 2 : kGraphSteps) && le == hipSuccess; ++j)
-        le = ctx_launch(c, c->two, (parity + j) & 1, c->cap_stream);
+    for (int j = 0; j < graph_steps(c) / c->fused && le == hipSuccess; ++j)
+        le = ctx_launch(c, c->fused > 1, (parity + j) & 1, c->cap_stream);
     e = hipStreamEndCapture(c->cap_stream, &graph);
     if (le != hipSuccess || e != hipSuccess) {
         if (graph) (void)hipGraphDestroy(graph);
@@ -625,7 +664,7 @@ int lbm_step(lbm_ctx *c, int64_t n)
     if (!c) return fail(nullptr, LBM_E_INVAL, "ctx is NULL");
     if (n < 0) return fail(c, LBM_E_INVAL, "n must be >= 0");
     DeviceGuard g(c->device);
-    while (n >= 2 * kGraphSteps) {
+    while (n >= 2 * graph_steps(c)) {
         const int par = (int)(c->steps & 1);
         if (!c->graph[par]) {
             int rc = build_graph(c, par);
@@ -633,17 +672,18 @@ int lbm_step(lbm_ctx *c, int64_t n)
         }
         hipError_t e = hipGraphLaunch(c->graph[par], c->stream);
         if (e != hipSuccess) return hip_fail(c, e, "hipGraphLaunch");
-        c->steps += kGraphSteps;
-        n -= kGraphSteps;
+        c->steps += graph_steps(c);
+        n -= graph_steps(c);
     }
-    // two-step launches go in pairs, so that the state stays in the buffer of
-    // the step counter's parity
-    for (; c->two && n >= 4; n -= 4) {
-        const int par = (int)(c->steps & 1);
-        hipError_t e = ctx_launch(c, true, par, c->stream);
-        if (e == hipSuccess) e = ctx_launch(c, true, par ^ 1, c->stream);
-        if (e != hipSuccess) return hip_fail(c, e, "step launch");
-        c->steps += 4;
+    // launches of an odd number of steps leave the state in the buffer of the
+    // step counter's parity, two-step launches do in pairs
+    const int pair = c->fused & 1 ? 1 : 2;
+    for (; c->fused > 1 && n >= pair * c->fused; n -= pair * c->fused) {
+        for (int j = 0; j < pair; ++j) {
+            hipError_t e = ctx_launch(c, true, (int)(c->steps & 1) ^ j, c->stream);
+            if (e != hipSuccess) return hip_fail(c, e, "step launch");
+        }
+        c->steps += pair * c->fused;
     }
     for (; n > 0; --n) {
         hipError_t e = ctx_launch(c, false, (int)(c->steps & 1), c->stream);

@@ -37,7 +37,7 @@ struct lbm_ctx {
     cgi::Layout lay{};
     int8_t *d_inlet = nullptr;
     cgd::SlotDesc desc{};               // geometry of the single-step launch
-    cgd::SlotDesc desc2{};              // and of the two-step launch (two)
+    cgd::SlotDesc desc2{};              // and of the fused launch (fused > 1)
     cgd::SlotDesc *d_desc = nullptr;    // both on the device
     float *d_fields = nullptr;          // 5 n floats: init input / moments output
     double *d_partial = nullptr;
@@ -47,7 +47,8 @@ struct lbm_ctx {
     int tx_req = 0, strip_req = 0;      // lbm_set_launch requests (0: planned)
     int xch_req = -1;                   // lbm_set_exchange request (-1: planned)
     bool xch = false;                   // planned: the exchange flavour (KV_XCH)
-    bool two = false;                   // planned: two steps per launch (KV_TWO) wherever a call has enough of them
+    int fused = 1;                      // planned: steps per launch wherever a call has enough of them
+    int fused_kv = 0;                   // its kernel variant (KV_TWO, KV_TILE)
     int tx2 = 0, tiles2 = 0;
     hipGraphExec_t graph[2] = {nullptr, nullptr};
     int graph_len = 0;
@@ -75,6 +76,9 @@ bool plan_two(long long nodes, int storage, int variant, int ny);
 int two_tx(int nx, int req);
 int two_waves(const lbm_params *p);
 int plan_two_strip(const lbm_params *p, long long nodes, long long wave_rows, int req);
+// Steps per launch of a workgroup that holds its rows (KV_TILE), 0: not for
+// this lattice; see cg_capi.cpp.
+int plan_tile(const lbm_params *p, int variant);
 // `paired`: the launch shares the chip with a second one (a batch's lanes);
 // `xch`: exchange flavour.
 int plan_strip(long long nodes, int ny, int tiles_x, int storage, int req, bool paired = false, bool xch = false);

@@ -13,6 +13,9 @@
 //              for lattices beyond the cache).
 //  k_step_two  two fused time steps in FP32 storage, the state between them in
 //              LDS (lattices that keep the chip full).
+//  k_step_tile two or three fused time steps in FP32 storage of lattices that do
+//              not fill the chip, one row per wavefront, the state between
+//              steps in LDS.
 //  k_init      equilibrium initialisation from FP32 fields.
 //  k_moments   fields at the current step (+ FP64 per-block diagnostics).
 //  k_reduce    fixed-order FP64 reduction of the per-block partials.
@@ -98,6 +101,30 @@ __device__ __forceinline__ void collide_store(const SlotDesc &S, const Halves &d
         collide_16<NSC>(S, cur, psi, Fx, Fy, k, nsc, dqx, dqy);
         store_16_node<ST>(S, dst, at, k.r, k.b, cur.mr, cur.mb);
     }
+}
+
+// Partial sums of one row that the divergence of Q needs (see step_body), and
+// dQx/dx, dQy/dy from three rows.  (no contraction, as gradient)
+struct QRow {
+    float d, s;
+};
+template <class Row>
+__device__ __forceinline__ void divergence(const Row &qb, const Row &q0, const Row &qa, float fd, float &dqx, float &dqy)
+{
+#pragma clang fp contract(off)
+    dqx = __builtin_fmaf(1.f / 3.f, q0.d, (1.f / 12.f) * (qa.d + qb.d));
+    dqy = fd * (qa.s - qb.s);
+}
+
+// Q of one node (see step_body)
+__device__ __forceinline__ void q_node(const SlotDesc &S, const Node &nd, float &qx, float &qy)
+{
+#pragma clang fp contract(off)
+    float ux, uy;
+    velocity(S, nd, nd.rr() + nd.rb(), ux, uy);
+    const float a = -(nd.rr() * S.k3[0] + nd.rb() * S.k3[1]);
+    qx = a * ux;
+    qy = a * uy;
 }
 
 // Colour field of one row as Psi3, and the halo nodes' values (lanes 0, 1,
@@ -262,14 +289,7 @@ __device__ __forceinline__ void step_nn(const SlotDesc *__restrict__ slots, int 
         return QRow{east_of(qx, hqx) - west_of(qx, hqx),
                     (1.f / 3.f) * qy + (1.f / 12.f) * (east_of(qy, hqy) + west_of(qy, hqy)), hqx, hqy};
     };
-    auto qnode = [&](const Node &nd, float &qx, float &qy) {
-#pragma clang fp contract(off)
-        float ux, uy;
-        velocity(S, nd, nd.rr() + nd.rb(), ux, uy);
-        const float a = -(nd.rr() * S.k3[0] + nd.rb() * S.k3[1]);
-        qx = a * ux;
-        qy = a * uy;
-    };
+    auto qnode = [&](const Node &nd, float &qx, float &qy) { q_node(S, nd, qx, qy); };
     // the ghost row's Q from the adjacent real row (its nodes and neighbour Q)
     auto qghost = [&](const Node &adj, const QRow &qa) -> QRow {
         float qx, qy, gx, gy, ghx, ghy;
@@ -432,8 +452,7 @@ __device__ __forceinline__ void step_nn(const SlotDesc *__restrict__ slots, int 
                             2u * ((uint32_t)y * (uint32_t)S.pitch + (uint32_t)xg)};
             float dqx = 0.f, dqy = 0.f;
             if constexpr (NSC) {
-                dqx = (1.f / 3.f) * q0.d + (1.f / 12.f) * (qa.d + qb.d);
-                dqy = fd * (qa.s - qb.s);
+                divergence(qb, q0, qa, fd, dqx, dqy);
             }
             collide_store<ST, NSC, kXchStorePolicy>(S, dst, at, cur, p0.c, Fx, Fy, nsc, dqx, dqy);
         }
@@ -523,22 +542,12 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
     // dQy/dy = s(y+1) - s(y-1) (the stencil of eq. (colorGradient)).  Ghost
     // rows beyond a wall take the colour field's extrapolation of Q.
     const bool nsc = NSC && (S.flags & F_NSC);
-    struct QRow {
-        float d, s;
-    };
     // (no contraction: every inlined copy must round alike, see step_nn)
     auto qrow = [&](float qx, float qy) -> QRow {
 #pragma clang fp contract(off)
         return QRow{from_east(qx) - from_west(qx), (1.f / 3.f) * qy + (1.f / 12.f) * (from_east(qy) + from_west(qy))};
     };
-    auto qnode = [&](const Node &nd, float &qx, float &qy) {
-#pragma clang fp contract(off)
-        float ux, uy;
-        velocity(S, nd, nd.rr() + nd.rb(), ux, uy);
-        const float a = -(nd.rr() * S.k3[0] + nd.rb() * S.k3[1]);
-        qx = a * ux;
-        qy = a * uy;
-    };
+    auto qnode = [&](const Node &nd, float &qx, float &qy) { q_node(S, nd, qx, qy); };
     auto qreal = [&](const Node &nd) -> QRow {
         float qx, qy;
         qnode(nd, qx, qy);
@@ -675,8 +684,7 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
                                 2u * ((uint32_t)y * (uint32_t)S.pitch + (uint32_t)xg)};
                 float dqx = 0.f, dqy = 0.f;
                 if constexpr (NSC) {
-                    dqx = (1.f / 3.f) * q0.d + (1.f / 12.f) * (qa.d + qb.d);
-                    dqy = fd * (qa.s - qb.s);
+                    divergence(qb, q0, qa, fd, dqx, dqy);
                 }
                 collide_store<ST, NSC>(S, dst, at, cur, c0, Fx, Fy, nsc, dqx, dqy);
             }
@@ -754,8 +762,7 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
                             2u * ((uint32_t)y * (uint32_t)S.pitch + (uint32_t)xg)};
             float dqx = 0.f, dqy = 0.f;
             if constexpr (NSC) {
-                dqx = (1.f / 3.f) * q0.d + (1.f / 12.f) * (qa.d + qb.d);
-                dqy = fd * (qa.s - qb.s);
+                divergence(qb, q0, qa, fd, dqx, dqy);
             }
             collide_store<ST, NSC>(S, dst, at, cur, p0.c, Fx, Fy, nsc, dqx, dqy);
         }
@@ -1045,6 +1052,155 @@ __device__ __forceinline__ void step_two(const SlotDesc *__restrict__ slots, int
     }
 }
 
+// T fused time steps of a lattice that does not fill the chip (FP32 storage).
+// One step of it takes the launch, two waits for memory and a row of
+// arithmetic at the rate of few wavefronts, whatever its size; here T steps
+// share the first two.  A workgroup of 16 wavefronts holds one row of 64
+// columns in each, and its state between steps in LDS (18 words per node): per
+// step every wavefront pulls its row, shares its colour field (and Q),
+// collides with those of the rows on either side and puts what it has.  Rows
+// and columns whose neighbours the workgroup does not hold drop out step by
+// step: of 16 x 64 nodes 6 x 54 (48 between walls) are left after three steps,
+// 10 x 58 (54) after two.  The nodes' arithmetic is the single step's, to the
+// bit.
+//
+// The wavefronts' registers and LDS fill a CU.  Measured, us per step, single
+// steps before against this: 64^2 4.9 -> 3.7, 100^2 with wetting walls and
+// correction 5.5 -> 4.1, 300 x 200 6.8 -> 4.05 (T = 3), 512^2 11.6 -> 9.5 (T =
+// 2).  What bounds it: the arithmetic of a row, 480 vector instructions a step
+// from four, then three, then two wavefronts a SIMD (2.5, 1.9 and 1.6 us), and
+// 5 us of launch and memory latency.
+template <int T, bool NSC>
+__device__ __forceinline__ void step_tile(const SlotDesc *__restrict__ slots, int nslots, int total_tiles, int parity)
+{
+    constexpr int ST = ST_F32, W = kTileRows;
+    __shared__ float pops[W * 18 * 64 + 2];
+    __shared__ float field[W * 64], fqx[NSC ? W * 64 : 1], fqy[NSC ? W * 64 : 1];
+
+    const int tile = xcd_tile(blockIdx.x, total_tiles);
+    const SlotDesc &S = slots[find_slot(slots, nslots, tile)];
+    const int lt = tile - S.tile_begin;
+    const int tyi = lt / S.tiles_x;
+    const int txi = lt - tyi * S.tiles_x;
+    const int nx = S.nx, ny = S.ny;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const bool yper = S.flags & F_YPER;
+    const bool xper = S.flags & F_XPER;
+    const bool nsc = NSC && (S.flags & F_NSC);
+    const int hl = tile_halo(T, yper);
+    const int xw = txi * tile_cols(T, yper);
+    const bool inlet_wave = xw == 0;
+    const int xl = xw - hl + lane;             // the lane's column (may lie outside the lattice)
+    const int xg = map_col(S, xl);
+    const bool out_lane = lane >= hl && lane < 64 - hl && xl < nx;
+    // the lane that holds the nearest column of the lattice, beyond an open face
+    const int near = xper ? lane : xg - (xw - hl);
+    const bool face = !xper && (xw - hl < 0 || xw - hl + 63 >= nx);
+    const XCols xc = make_cols<ST>(S, xg);
+    const Halves src = halves<ST>(S, parity ? S.buf[1] : S.buf[0]);
+    const Halves dst = halves<ST>(S, parity ? S.buf[0] : S.buf[1]);
+
+    const int yl = tyi * tile_out(T) - (2 * T - 1) + w;   // the wavefront's row
+    const bool row = yper || (yl >= 0 && yl < ny);
+    const int y = yper ? wrap_near(yl, ny) : yl;
+    const bool wlo = !yper && yl == 0, whi = !yper && yl == ny - 1;
+
+    // wall ghost rows (see step_body)
+    const bool in0 = xper || (xl >= 0 && xl < nx);
+    const bool inw = xper || (xl - 1 >= 0 && xl - 1 < nx);
+    const bool ine = xper || (xl + 1 >= 0 && xl + 1 < nx);
+    const float gden = (in0 ? 4.f : 0.f) + (inw ? 1.f : 0.f) + (ine ? 1.f : 0.f);
+    const float ginv = gden > 0.f ? fast_rcp(gden) : 0.f;
+    auto ghost_of = [&](float c) -> float {
+        const float e0 = from_west(c), e1 = from_east(c);
+        return ((in0 ? 4.f * c : 0.f) + (inw ? e0 : 0.f) + (ine ? e1 : 0.f)) * ginv;
+    };
+    auto qrow = [&](float qx, float qy) -> QRow {
+#pragma clang fp contract(off)
+        return QRow{from_east(qx) - from_west(qx), (1.f / 3.f) * qy + (1.f / 12.f) * (from_east(qy) + from_west(qy))};
+    };
+
+    // Word of lane l, row r, population i and colour half k.  Lanes 0 and 63
+    // reach into a neighbouring word (or the one before or after the array):
+    // what they read there is never used.
+    auto at_word = [&](int r, int i, int k) { return 1 + ((r * 9 + i) * 2 + k) * 64 + lane; };
+
+    RowSrc rw{};
+    if (row) rw = make_row<ST>(S, y, inlet_wave);
+#pragma unroll 1
+    for (int t = 0; t < T; ++t) {
+        // rows whose populations of step t are known, and of those the ones
+        // whose neighbours' colour field is
+        const bool known = row && w >= 2 * t && w < W - 2 * t;
+        const bool inner = row && w >= 2 * t + 1 && w < W - 2 * t - 1;
+        Node nd;
+        float p0 = 0.f, qx = 0.f, qy = 0.f;
+        if (known) {
+            Raw18<ST> raw;
+            if (t == 0) {
+                raw = issue<ST>(S, src, xc, rw);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 9; ++i) {
+                    const int from = at_word(w - cy(i), i, 0) - cx(i);
+                    raw.v[i] = __float_as_uint(pops[from]);
+                    raw.v[9 + i] = __float_as_uint(pops[from + 64]);
+                }
+                if (wlo || whi) {              // beyond a wall as in issue()
+#pragma unroll
+                    for (int i = 0; i < 9; ++i) {
+                        if (cy(i) > 0 ? !wlo : (cy(i) < 0 ? !whi : true)) continue;
+                        const bool fs = cx(i) != 0 && (S.flags & (cy(i) > 0 ? F_SLIP_LO : F_SLIP_HI));
+                        const int from = fs ? at_word(w, mirror_y(i), 0) - cx(i) : at_word(w, opp(i), 0);
+                        raw.v[i] = __float_as_uint(pops[from]);
+                        raw.v[9 + i] = __float_as_uint(pops[from + 64]);
+                    }
+                }
+            }
+            nd = finish<ST>(S, raw, xc, rw);
+            p0 = color_field<ST>(S, nd.rr(), nd.rb());
+            if (nsc) q_node(S, nd, qx, qy);
+            if (face && t > 0) {
+                p0 = __shfl(p0, near, 64);
+                if (nsc) {
+                    qx = __shfl(qx, near, 64);
+                    qy = __shfl(qy, near, 64);
+                }
+            }
+            field[w * 64 + lane] = p0;
+            if (nsc) {
+                fqx[w * 64 + lane] = qx;
+                fqy[w * 64 + lane] = qy;
+            }
+        }
+        __syncthreads();                       // the colour field is there, and all have pulled
+        if (inner) {
+            const float pb = wlo ? ghost_of(p0) : field[(w - 1) * 64 + lane];
+            const float pa = whi ? ghost_of(p0) : field[(w + 1) * 64 + lane];
+            float Fx, Fy, dqx = 0.f, dqy = 0.f;
+            gradient(psi3(pb), psi3(p0), psi3(pa), 1.f, Fx, Fy);
+            if ((S.flags & F_WET) && (y == 0 || y == ny - 1)) wet(S, y == 0, Fx, Fy);
+            if (nsc) {
+                const QRow qb = wlo ? qrow(ghost_of(qx), ghost_of(qy))
+                                    : qrow(fqx[(w - 1) * 64 + lane], fqy[(w - 1) * 64 + lane]);
+                const QRow qa = whi ? qrow(ghost_of(qx), ghost_of(qy))
+                                    : qrow(fqx[(w + 1) * 64 + lane], fqy[(w + 1) * 64 + lane]);
+                divergence(qb, qrow(qx, qy), qa, 1.f, dqx, dqy);
+            }
+            const Post P = collide<NSC>(S, nd, p0, Fx, Fy, nsc, dqx, dqy);
+            if (t < T - 1) {
+                put_f32_node(P, nd.mr, nd.mb, [&](int i, int k, float v) { pops[at_word(w, i, k)] = v; });
+            } else if (yl < ny) {              // a last tile's rows beyond a periodic lattice are another's
+                const NodeAt at{out_lane ? xc.o0 : kNoStore, xc.r0, (uint32_t)y * (uint32_t)S.row_bytes,
+                                2u * ((uint32_t)y * (uint32_t)S.pitch + (uint32_t)xg)};
+                store_f32_node(dst, at, P, nd.mr, nd.mb);
+            }
+        }
+        if (t < T - 1) __syncthreads();
+    }
+}
+
 // Register budgets: the variants without the Navier-Stokes correction fit
 // 128 VGPRs, i.e. 4 wavefronts per SIMD, without spilling and are capped
 // there; the corrected ones keep their natural allocation (3 per SIMD; the
@@ -1064,6 +1220,13 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 
 k_step(const SlotDesc *__restrict__ slots, int nslots, int total_tiles, int parity, int launch_idx)
 {
     step_any<ST, W, KV>(slots, nslots, total_tiles, parity, launch_idx);
+}
+
+template <int T, bool NSC>
+__global__ void __launch_bounds__(64 * kTileRows) __attribute__((amdgpu_waves_per_eu(4, 4)))
+k_step_tile(const SlotDesc *__restrict__ slots, int nslots, int total_tiles, int parity)
+{
+    step_tile<T, NSC>(slots, nslots, total_tiles, parity);
 }
 
 template <int W>
@@ -1305,6 +1468,14 @@ static hipError_t step_two_tx(int tx, const SlotDesc *d, int nslots, int tiles, 
     return hipGetLastError();
 }
 
+template <int ST, int T, bool NSC>
+static hipError_t step_tile_v(int tx, const SlotDesc *d, int nslots, int tiles, int parity, hipStream_t s)
+{
+    if (ST != ST_F32 || tx != 64 * kTileRows) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_step_tile<T, NSC>), dim3(tiles), dim3(tx), 0, s, d, nslots, tiles, parity);
+    return hipGetLastError();
+}
+
 template <int ST>
 static hipError_t step_st(int tx, const SlotDesc *d, int nslots, int tiles, int parity, int idx, hipStream_t s,
                           int variant)
@@ -1316,6 +1487,10 @@ static hipError_t step_st(int tx, const SlotDesc *d, int nslots, int tiles, int 
     case KV_NSC | KV_ISO: return step_v<ST, KV_NSC | KV_ISO>(tx, d, nslots, tiles, parity, idx, s);
     case KV_XCH: return step_v<ST, KV_XCH>(tx, d, nslots, tiles, parity, idx, s);
     case KV_XCH | KV_NSC: return step_v<ST, KV_XCH | KV_NSC>(tx, d, nslots, tiles, parity, idx, s);
+    case KV_TILE: return step_tile_v<ST, 3, false>(tx, d, nslots, tiles, parity, s);
+    case KV_TILE | KV_NSC: return step_tile_v<ST, 3, true>(tx, d, nslots, tiles, parity, s);
+    case KV_TILE | KV_TWO: return step_tile_v<ST, 2, false>(tx, d, nslots, tiles, parity, s);
+    case KV_TILE | KV_TWO | KV_NSC: return step_tile_v<ST, 2, true>(tx, d, nslots, tiles, parity, s);
     case KV_TWO: return ST == ST_F32 ? step_two_tx(tx, d, nslots, tiles, parity, s) : hipErrorInvalidValue;
     }
     return hipErrorInvalidValue;

@@ -14,8 +14,10 @@ namespace cgd {
 // LDS (full-line stores, for lattices beyond the cache), instead of holding
 // halo columns in their own outer lanes.  Both give the same bits.
 // KV_TWO (FP32 storage, nearest-neighbour gradient, no correction) is a
-// launch choice as well: one launch advances two steps, the state between them in LDS.
-enum : int { KV_NSC = 1, KV_ISO = 2, KV_XCH = 4, KV_TWO = 8 };
+// launch choice as well: one launch advances two steps, the state between them in LDS;
+// KV_TILE (FP32 storage, nearest-neighbour gradient, with or without KV_NSC)
+// advances three, with KV_TWO two.
+enum : int { KV_NSC = 1, KV_ISO = 2, KV_XCH = 4, KV_TWO = 8, KV_TILE = 16 };
 // The variant a lattice needs alone.
 inline int step_variant(const SlotDesc &d)
 {
