@@ -265,11 +265,12 @@ __device__ __forceinline__ void enc_pair(const SlotDesc &S, int c, float vr, flo
                                          uint16_t &q, uint16_t &u, float &nr, float &nb)
 {
     const float n = vr + vb;
-    float g = vr * __builtin_amdgcn_rcpf(n);
-    g = g > 0.f ? (g < 1.f ? g : 1.f) : 0.f;          // NaN -> 0 (its N stays NaN)
-    g = vb == 0.f ? 1.f : (vr == 0.f ? 0.f : g);       // an absent colour stays exactly absent
+    // [0, 1], NaN -> 0 (its N stays NaN); an absent colour stays exactly absent
+    // (red one: 0 or NaN from the product)
+    float g = __builtin_amdgcn_fmed3f(vr * __builtin_amdgcn_rcpf(n), 0.f, 1.f);
+    g = vb == 0.f ? 1.f : g;
     // dither in [0, 1) from the top 23 bits (as the mantissa of a number in [1, 2))
-    const float dith = sr ? __uint_as_float(0x3f800000u | (rg >> 9)) - 1.f : 0.5f;
+    const float dith = sr ? __uint_as_float(__builtin_amdgcn_alignbit(0x7fu, rg, 9)) - 1.f : 0.5f;
     const uint32_t ui = (uint32_t)__builtin_fmaf(g, 65535.f, dith);   // g in [0,1]: 0 .. 65535
     u = (uint16_t)(ui > 65535u ? 65535u : ui);
     const float x = (n - S.mref[c]) * S.dscale;
@@ -284,11 +285,8 @@ __device__ __forceinline__ void enc_pair(const SlotDesc &S, int c, float vr, flo
 // two ulps), stochastically with the dither r01 in [0, 1) (0.5: to nearest):
 // forcing the bit onto a rounded value would bias the rest, and with it the
 // colour mass, at every node and step.
-__device__ __forceinline__ uint32_t enc_rest(double v, float ref, double r01)
+__device__ __forceinline__ uint32_t round_rest(double a, uint32_t flag, double r01)
 {
-    const uint32_t flag = fabs(v - (double)ref) < fabs(v) ? 1u : 0u;
-    const double t = flag ? v - (double)ref : v;
-    const double a = fabs(t);
     const uint32_t m = __float_as_uint((float)a);
     uint32_t lo, hi;
     if ((m & 1u) == flag) {
@@ -300,8 +298,32 @@ __device__ __forceinline__ uint32_t enc_rest(double v, float ref, double r01)
     }
     if (lo > hi) lo = flag;   // below the smallest magnitude of the grid
     const double vlo = (double)__uint_as_float(lo), vhi = (double)__uint_as_float(hi);
-    const uint32_t mm = (a - vlo) > r01 * (vhi - vlo) ? hi : lo;
-    return mm | (t < 0.0 ? 0x80000000u : 0u);
+    return (a - vlo) > r01 * (vhi - vlo) ? hi : lo;
+}
+// The same of v, with the flag chosen and the dither r24 2^-24, in integer
+// arithmetic on the FP64 bits, where an FP32 ulp is 2^29: adding one less than
+// the threshold of a two-ulp cell and truncating rounds up exactly where the
+// comparison above does, in half its instructions.  Cells that reach across a
+// power of two, whose ulps differ, and values outside the normal FP32 range
+// take the comparison.
+__device__ __forceinline__ uint32_t enc_rest(double v, float ref, uint32_t r24)
+{
+    const double dev = v - (double)ref;
+    const bool fl = fabs(dev) < fabs(v);
+    const double t = fl ? dev : v;
+    const uint32_t flag = fl ? 1u : 0u;
+    const uint64_t bits = (uint64_t)__double_as_longlong(t);
+    const uint32_t sign = (uint32_t)(bits >> 32) & 0x80000000u, hi = (uint32_t)(bits >> 32) & 0x7fffffffu;
+    const uint64_t a = (((uint64_t)hi << 32) | (uint32_t)bits) - ((uint64_t)flag << 29);
+    const uint64_t up = a + (0x3fffffffu - (r24 << 6));
+    // (the cell's lower end; exponent bias 1023 -> 127)
+    const uint32_t lo = (((uint32_t)(a >> 29) - (896u << 23)) & ~1u) | flag;
+    const uint32_t m = (((uint32_t)(up >> 29) - (896u << 23)) & ~1u) | flag;
+    if (hi - 0x38200000u >= 0x47e00000u - 0x38200000u || (lo & 0x7fffffu) >= 0x7ffffeu) {
+        if (t == 0.0) return flag;
+        return round_rest(fabs(t), flag, (double)r24 * 0x1p-24) | (t < 0.0 ? 0x80000000u : 0u);
+    }
+    return m | sign;
 }
 // decoded rest population (FP32) and its exact value (FP64)
 __device__ __forceinline__ float dec_rest(uint32_t b, float ref, double &exact)
@@ -800,9 +822,9 @@ __device__ __forceinline__ void store18_nearest(const SlotDesc &S, const Halves 
             C::put(q, h.r[0], at.col, plane_off<ST>(i) + at.row);
             C::put(u, h.r[1], at.col, plane_off<ST>(i) + at.row);
         }
-        __builtin_amdgcn_raw_buffer_store_b32(enc_rest((double)outr[0], S.rest0[0], 0.5), h.r[0], (int)at.rcol,
+        __builtin_amdgcn_raw_buffer_store_b32(enc_rest((double)outr[0], S.rest0[0], 1u << 23), h.r[0], (int)at.rcol,
                                               (int)at.row, CG_STORE_POLICY);
-        __builtin_amdgcn_raw_buffer_store_b32(enc_rest((double)outb[0], S.rest0[1], 0.5), h.r[1], (int)at.rcol,
+        __builtin_amdgcn_raw_buffer_store_b32(enc_rest((double)outb[0], S.rest0[1], 1u << 23), h.r[1], (int)at.rcol,
                                               (int)at.row, CG_STORE_POLICY);
     }
 }
@@ -1184,11 +1206,22 @@ __device__ __forceinline__ void store_f32_node(const Halves &h, const NodeAt &at
     });
 }
 
+// c_i . (x, y), with no products of zero components
+__device__ __forceinline__ constexpr float along(int i, float x, float y)
+{
+    return cy(i) == 0 ? (cx(i) == 0 ? 0.f : cx(i) * x) : (cx(i) == 0 ? cy(i) * y : cx(i) * x + cy(i) * y);
+}
+
 // The same of a lattice in 16-bit storage, direction by direction; each output
 // pair (post-recolouring red and blue populations) goes to sink(i, red, blue).
 // The encoder's dither is seeded by the bits of these outputs, so another
-// rounding anywhere in here is another sequence of dithers: the expressions
-// stay as they are.
+// rounding anywhere in here is another sequence of dithers: the fused
+// multiply-adds are spelled out, or (MRT, correction) the expressions left as
+// the compiler contracts them.  Bound by instruction issue together with the
+// codec; skipping perturbation and segregation away from interfaces, their
+// terms formed once per pair of directions, and the codec's clamps took the
+// 4096 x 256 slug channel from 33.0 to 30.6 us a step, the 8192 x 512 channel
+// from 107 to 103.
 template <bool NSC = false, class Sink>
 __device__ __forceinline__ void collide_16(const SlotDesc &S, const Node &nd, float psi, float Fx, float Fy, Sink &&sink,
                                         bool nsc = false, float dqx = 0.f, float dqy = 0.f)
@@ -1216,7 +1249,6 @@ __device__ __forceinline__ void collide_16(const SlotDesc &S, const Node &nd, fl
     const float K = herm ? rr * S.k3[0] + rb * S.k3[1] : 0.f;
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
-        const float cu = cx(i) * ux + cy(i) * uy;
         const int c = vclass(i);
         // N - N^(e) with the rest part subtracted by fused multiply-adds: the
         // large rest populations of a heavy fluid never get rounded on their own
@@ -1224,10 +1256,17 @@ __device__ __forceinline__ void collide_16(const SlotDesc &S, const Node &nd, fl
         t = __builtin_fmaf(-rb, S.phi[1][c], t);
         // unit mass of the FP32 rest weights, and the exact mass of the node
         if (i == 0) t -= rr * S.phi0_eps[0] + rb * S.phi0_eps[1] + nd.dm();
-        if (herm && i != 0)
-            neq[i] = t - wgt(i) * (3.f * cu * __builtin_fmaf(hco(i), K, rho) + rho * (4.5f * cu * cu - 1.5f * uu));
-        else
-            neq[i] = t - rho * wgt(i) * (3.f * cu + 4.5f * cu * cu - 1.5f * uu);
+        if constexpr (NSC) {
+            const float cu = cx(i) * ux + cy(i) * uy;
+            if (herm && i != 0)
+                neq[i] = t - wgt(i) * (3.f * cu * __builtin_fmaf(hco(i), K, rho) + rho * (4.5f * cu * cu - 1.5f * uu));
+            else
+                neq[i] = t - rho * wgt(i) * (3.f * cu + 4.5f * cu * cu - 1.5f * uu);
+        } else {
+            const float cu = along(i, ux, uy);
+            const float e = __builtin_fmaf(-1.5f, uu, __builtin_fmaf(3.f, cu, 4.5f * cu * cu));
+            neq[i] = __builtin_fmaf(-(rho * wgt(i)), e, t);
+        }
     }
     float ns[9];
     if (S.flags & F_MRT) {
@@ -1279,31 +1318,41 @@ __device__ __forceinline__ void collide_16(const SlotDesc &S, const Node &nd, fl
     const float cmin = (red_minor ? rr : rb) * irho;    // 0 exactly for an absent colour
     const float cmaj = (red_minor ? rb : rr) * irho;
     const float sgn = red_minor ? 1.f : -1.f;           // the segregation term adds to red
-    // no gradient (|F| <= 1e-12): neither perturbation nor segregation.  Both
-    // forms are evaluated and selected per lane (uniform control flow, so that
-    // every store of a row is one instruction over the whole wavefront).
-    const bool pert = F2 > 1e-24f;
-    const float inv = pert ? __builtin_amdgcn_rsqf(F2) : 0.f;   // 1/|F|
-    const float Fm = F2 * inv;                                   // |F|
-    const float A = (S.flags & F_SIGMA) ? S.sigma94 * w : S.A;
-    const float seg = S.beta * cmin * cmaj;
+    // no gradient (|F| <= 1e-12): neither perturbation nor segregation, which
+    // wavefronts away from interfaces skip
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
-        const float fc = cx(i) * Fx + cy(i) * Fy;
-        const float nss = ns[i] + A * (wgt(i) * fc * fc * inv - bco(i) * Fm);
-        float sg = 0.f;
-        if (i != 0) {
+        const float mino = cmin * ns[i];
+        const float majo = __builtin_fmaf(-cmin, ns[i], ns[i]);
+        sink(i, red_minor ? mino : majo, red_minor ? majo : mino);
+    }
+    if (F2 > 1e-24f) {
+        const float inv = __builtin_amdgcn_rsqf(F2);             // 1/|F|
+        const float Fm = F2 * inv;                               // |F|
+        const float A = (S.flags & F_SIGMA) ? S.sigma94 * w : S.A;
+        const float seg = S.beta * cmin * cmaj;
+        // even part of the perturbation and segregation of directions 1, 2, 5, 6;
+        // the opposite directions' are the same and the negative
+        float pt[9], sgs[9];
+#pragma unroll
+        for (int i = 1; i < 9; ++i) {
+            if (i == 3 || i == 4 || i == 7 || i == 8) continue;
+            const float fc = along(i, Fx, Fy);
+            pt[i] = pt[opp(i)] = __builtin_fmaf(wgt(i) * fc * fc, inv, -(bco(i) * Fm));
             const int c = vclass(i);
             const float cosphi = fc * inv * (c == 1 ? 1.f : 0.70710678118654752f);
-            sg = seg * cosphi * (rr * S.phi[0][c] + rb * S.phi[1][c]);
+            sgs[i] = seg * cosphi * __builtin_fmaf(rr, S.phi[0][c], rb * S.phi[1][c]);
+            sgs[opp(i)] = -sgs[i];
         }
-        const float mino_p = cmin * nss + sgn * sg;
-        const float majo_p = nss - mino_p;
-        const float mino_0 = cmin * ns[i];
-        const float majo_0 = ns[i] - mino_0;
-        const float mino = pert ? mino_p : mino_0;
-        const float majo = pert ? majo_p : majo_0;
-        sink(i, red_minor ? mino : majo, red_minor ? majo : mino);
+        pt[0] = -(bco(0) * Fm);
+        sgs[0] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            const float nss = __builtin_fmaf(A, pt[i], ns[i]);
+            const float mino = __builtin_fmaf(cmin, nss, sgn * sgs[i]);
+            const float majo = nss - mino;
+            sink(i, red_minor ? mino : majo, red_minor ? majo : mino);
+        }
     }
 }
 
@@ -1341,10 +1390,8 @@ __device__ __forceinline__ void put_16_node(const SlotDesc &S, uint32_t pos, con
         ab += (double)nb;
         put(i, q, u);
     }
-    const uint32_t r1 = weyl(seed, 18), r2 = weyl(seed, 19);
-    const double d1 = CG_CODEC_SR ? (double)(r1 >> 8) * 0x1p-24 : 0.5, d2 = CG_CODEC_SR ? (double)(r2 >> 8) * 0x1p-24 : 0.5;
-    rest(0, enc_rest(mr - ar, S.rest0[0], d1));
-    rest(1, enc_rest(mb - ab, S.rest0[1], d2));
+    rest(0, enc_rest(mr - ar, S.rest0[0], CG_CODEC_SR ? weyl(seed, 18) >> 8 : 1u << 23));
+    rest(1, enc_rest(mb - ab, S.rest0[1], CG_CODEC_SR ? weyl(seed, 19) >> 8 : 1u << 23));
 }
 
 // The same to a population buffer.

@@ -507,8 +507,9 @@ __device__ __forceinline__ void step_body(const SlotDesc *__restrict__ slots, in
     // stores (and a loop entered without any) would leave the compiler unable
     // to tell how many stores are younger than the row's loads: it then waits
     // for all of them to complete, every row, before it uses what was loaded.
-    // (16-bit storage keeps the branch: its collision is contracted by the
-    // compiler, and where the block of code begins is part of how it rounds,
+    // (16-bit storage keeps the branch: without it the slug channel takes 1.6%
+    // longer and the others the same; the corrected collision is contracted by
+    // the compiler, and where its block of code begins is part of how it rounds,
     // hence of the dither, see collide_16.)
     constexpr bool kMasked = ST == ST_F32;
     const uint32_t col_out = kMasked && !out_lane ? kNoStore : xc.o0;
