@@ -628,8 +628,10 @@ def main():
                 "kernel": "k_step", "flavour": m["flavour"], "launches_per_step": m["launches"],
                 "launch_us" if m["launches"] == 1 else "step_us": m["ms_per_step"] * 1e3,
                 "kernel_hash": kernel_hash(),
-                "definition": "achieved = bytes_per_update x lattice nodes of one launch / average launch "
-                              "duration (HIP events around the timed launches on their stream)"
+                "definition": "achieved = bytes_per_update x lattice nodes / average time per step (HIP events "
+                              "around the timed launches on their stream); FP32 launches that advance two "
+                              "steps move the state once for both, so that less than this is moved "
+                              "(traffic: measured bytes per step)"
                               if m["launches"] == 1 else
                               "achieved = bytes_per_update x nodes of one step / step time (several launches "
                               "per step, two in flight on two streams)"}

@@ -203,7 +203,11 @@ int lbm_load_state(lbm_ctx *ctx, const void *host, size_t n);
 
 /* Launch-shape control (tuning): threads per workgroup (64, 128, 256, 512 or
  * 1024: one to sixteen wavefronts side by side; 0 = planned) and rows per
- * workgroup strip (0 = planned).  Results do not depend on either. */
+ * workgroup strip (0 = planned).  Results do not depend on either, nor on how
+ * many steps a launch advances: in FP32 storage with the nearest-neighbour
+ * gradient, calls of several steps advance two or three per launch on lattices
+ * that do not fill the chip (planned launch shape only) and two on lattices of
+ * 500 000 nodes and more without the Navier-Stokes correction. */
 int lbm_set_launch(lbm_ctx *ctx, int32_t tile_x, int32_t strip_rows);
 /* Step-kernel flavour (tuning; nearest-neighbour gradient only -- the
  * second-neighbour gradient always uses halo lanes): 1 = block exchange (each
@@ -212,8 +216,9 @@ int lbm_set_launch(lbm_ctx *ctx, int32_t tile_x, int32_t strip_rows);
  * cache lines written, for lattices beyond the last-level cache), 0 = halo
  * lanes (each wavefront writes 60 columns and its outer lanes hold the
  * neighbour columns), -1 = planned (block exchange for FP32 storage without
- * the Navier-Stokes correction when both population buffers exceed 256 MiB).
- * Results do not depend on it.
+ * the Navier-Stokes correction when both population buffers exceed 256 MiB;
+ * steps that a launch of several takes are not its).  0 and 1 keep every step
+ * of lbm_step a launch of its own.  Results do not depend on it.
  * Errors: LBM_E_INVAL for another mode. */
 int lbm_set_exchange(lbm_ctx *ctx, int32_t mode);
 /* The HIP stream of the context (a hipStream_t). */
@@ -221,7 +226,8 @@ void *lbm_stream(const lbm_ctx *ctx);
 
 /* ---- batched stepping -------------------------------------------------
  * A batch advances several contexts (same device, same storage type) with one
- * kernel launch per group of lattices and time step: every workgroup finds
+ * kernel launch per group of lattices and time step (FP32 groups with 500 000
+ * nodes and more in flight: per two time steps): every workgroup finds
  * its lattice in a device table of lattice descriptors.  A batch of two or more lattices is split
  * into groups (contiguous, balanced by bytes, at least two, never mixing
  * kernel variants) sized so that two groups fit MI355X's 256 MB Infinity

@@ -212,29 +212,28 @@ int default_tx(int nx, int ny) { return (long long)nx * ny >= (1LL << 22) ? 256 
 // lattice) exceed the 256 MB Infinity Cache: there each row of a plane must
 // be written in whole cache lines, and the halo-lane flavour's stores, which
 // split lines between wavefronts, cost a read-modify-write in DRAM (8192 x
-// 512 channel 33k against 27k MLUPS; 8192^2 bubble 36k against 28k).  The
+// 512 channel 125 us a step against 155; 8192^2 bubble 36k MLUPS against
+// 28k).  It takes the steps that two-step launches (plan_two) leave over.  The
 // halo lanes stay the choice inside the cache (no barrier, no halo gather on
-// the row's critical path: 4096 x 256 slug, 151 MB, 35.8k against 29.7k);
-// for 16-bit storage, whose step is bound by its codec's arithmetic and pays
-// more for the per-row barrier than it saves (channel 39.4k against 34.1k);
-// with the Navier-Stokes correction, whose exchange step needs more than
-// 128 VGPRs, 3 wavefronts per SIMD and at most 8 per workgroup (channel
-// 27.9k against 22.7k); and with the 25-point isotropic gradient, for which
-// the exchange flavour is not built (its two-column halo stays in lanes).
+// the row's critical path: 4096 x 256 slug, 151 MB, 35.8k against 29.7k); for
+// 16-bit storage, whose step is bound by its codec's arithmetic and pays more
+// for the per-row barrier than it saves; with the 25-point isotropic gradient,
+// for which the exchange flavour is not built (its two-column halo stays in
+// lanes); and with the Navier-Stokes correction, where the exchange flavour is
+// for the asking (lbm_set_exchange; on the corrected channel 134 us against
+// 152 with 1024 columns).
 bool plan_exchange(size_t bytes, int storage, int variant)
 {
     return storage == LBM_STORE_F32 && !(variant & (cgd::KV_ISO | cgd::KV_NSC)) && bytes > kXchBytes;
 }
 
 // Exchange flavour: the widest workgroup (up to 16 wavefronts, 1024 columns)
-// that still leaves several workgroups across the lattice; at most 8 with the
-// Navier-Stokes correction, whose step needs more than the 128 VGPRs per lane
-// that 16 wavefronts on a CU leave (a 1024-thread workgroup would spill).
-// Lattices tall enough for four or more 1024-column workgroups of 16-row
-// strips per CU take 512 columns: two workgroups share a CU, and one's
-// barriers overlap the other's work (8192^2: 36.2k MLUPS against 34.6k;
-// the 8192 x 512 channel, one workgroup per CU, keeps 1024: 32.7k against
-// 31.3k).
+// that still leaves several workgroups across the lattice; at most 8 planned
+// with the Navier-Stokes correction.  Lattices tall enough for four or more
+// 1024-column workgroups of 16-row strips per CU take 512 columns: two
+// workgroups share a CU, and one's barriers overlap the other's work (8192^2:
+// 36.2k MLUPS against 34.6k; the 8192 x 512 channel, one workgroup per CU,
+// keeps 1024: 32.7k against 31.3k).
 int xch_tx(int nx, int ny, int variant)
 {
     const int blocks = (nx + 63) / 64;
