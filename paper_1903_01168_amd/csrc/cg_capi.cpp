@@ -323,30 +323,35 @@ int plan_two_strip(const lbm_params *p, long long nodes, long long wave_rows, in
     return std::min(s, p->ny);
 }
 
-static void tile_grid(const lbm_params *p, int T, int &tx, int &ty)
+static void tile_grid(const lbm_params *p, int T, int wg_rows, int &tx, int &ty)
 {
-    const int cols = cgd::tile_cols(T, p->bc_ylo == LBM_BC_PERIODIC), rows = cgd::tile_out(T);
+    const int cols = cgd::tile_cols(T, p->bc_ylo == LBM_BC_PERIODIC), rows = cgd::tile_out(T, wg_rows);
     tx = (p->nx + cols - 1) / cols;
     ty = (p->ny + rows - 1) / rows;
 }
 
-// Two or three steps per launch, one row per wavefront.  A workgroup takes a
-// CU, so a launch takes whole rounds of 256 of them, whatever they hold: 2.0 +
-// 10 us for three steps in one round, 2.0 + 8 us for two (us per step, one
-// step a launch against three and two: 64^2 4.9 / 3.7 / 4.5, 200^2 5.8 / 3.9,
-// 300 x 200 6.8 / 4.05 / 5.1, 320^2 8.4 / 7.1 in two rounds / 5.2 in one;
-// with walls, wetting and correction 64^2 5.3 / 4.0, 300 x 200 7.2 / 4.3, 400
-// x 300 8.7 / 7.8 / 5.7).  Two rounds of two steps pay from 180 000 nodes (400
-// x 400 9.26 / 9.26, 512 x 400 9.9 / 9.3, 512^2 11.6 / 9.5, with correction
-// and walls 1024 x 256 12.4 / 10.2), three do not (512^2 between walls 12.4 /
-// 13.9, 600^2 13.8 / 13.3, 700 x 640 15.7 / 17.1).
-int plan_tile(const lbm_params *p, int variant)
+// Two or three steps per launch, one row per wavefront of a workgroup of
+// `rows`.  A workgroup takes a CU, so a launch takes whole rounds of 256 of
+// them, whatever they hold: 9.5 us for three steps of 12 rows, 12 of 16, 10
+// for two of 16 (us per step, one step a launch against three of 12, three of
+// 16, two of 16: 64^2 4.9 / 3.15 / 3.7 / 4.5, 128^2 5.2 / 3.2 / 3.75 / 4.7,
+// 200^2 5.8 / - / 3.9, 300 x 200 6.8 / - / 4.05 / 5.1, 320^2 8.4 / - / 7.1 in
+// two rounds / 5.2; with walls, wetting and correction 64^2 5.3 / 3.4 / 4.0,
+// 300 x 200 7.2 / - / 4.3, 400 x 300 8.7 / - / 7.8 / 5.7).  Two rounds of two
+// steps pay from 180 000 nodes (400 x 400 9.26 / 9.26, 512 x 400 9.9 / 9.3,
+// 512^2 11.6 / 9.5, with correction and walls 1024 x 256 12.4 / 10.2), three
+// do not (512^2 between walls 12.4 / 13.9, 600^2 13.8 / 13.3, 700 x 640 15.7 /
+// 17.1).
+int plan_tile(const lbm_params *p, int variant, int &rows)
 {
     if (p->storage != LBM_STORE_F32 || (variant & cgd::KV_ISO) || p->ny < 4) return 0;
     int tx, ty;
-    tile_grid(p, 3, tx, ty);
-    if ((long long)tx * ty <= 256) return 3;
-    tile_grid(p, 2, tx, ty);
+    for (rows = 12; rows <= 16; rows += 4) {
+        tile_grid(p, 3, rows, tx, ty);
+        if ((long long)tx * ty <= 256) return 3;
+    }
+    rows = 16;
+    tile_grid(p, 2, rows, tx, ty);
     if ((long long)tx * ty <= 256) return 2;
     return (long long)tx * ty <= 512 && (long long)p->nx * p->ny >= 180000 ? 2 : 0;
 }
@@ -420,13 +425,14 @@ static int replan(lbm_ctx *c)
     const long long nodes = (long long)c->p.nx * c->p.ny;
     c->fused = 1;
     c->desc2 = c->desc;
-    const int T = c->xch_req < 0 && !c->tx_req && !c->strip_req ? plan_tile(&c->p, var) : 0;
+    int tile_rows = 0;
+    const int T = c->xch_req < 0 && !c->tx_req && !c->strip_req ? plan_tile(&c->p, var, tile_rows) : 0;
     if (T) {
         c->fused = T;
         c->fused_kv = cgd::KV_TILE | (T == 2 ? cgd::KV_TWO : 0) | var;
-        c->tx2 = 64 * cgd::kTileRows;
-        c->desc2.strip = cgd::tile_out(T);
-        tile_grid(&c->p, T, c->desc2.tiles_x, c->desc2.tiles_y);
+        c->tx2 = 64 * tile_rows;
+        c->desc2.strip = cgd::tile_out(T, tile_rows);
+        tile_grid(&c->p, T, tile_rows, c->desc2.tiles_x, c->desc2.tiles_y);
     } else if (c->xch_req < 0 && plan_two(nodes, c->p.storage, var, c->p.ny)) {
         c->fused = 2;
         c->fused_kv = cgd::KV_TWO;

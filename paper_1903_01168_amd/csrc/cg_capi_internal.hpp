@@ -78,7 +78,7 @@ int two_waves(const lbm_params *p);
 int plan_two_strip(const lbm_params *p, long long nodes, long long wave_rows, int req);
 // Steps per launch of a workgroup that holds its rows (KV_TILE), 0: not for
 // this lattice; see cg_capi.cpp.
-int plan_tile(const lbm_params *p, int variant);
+int plan_tile(const lbm_params *p, int variant, int &rows);
 // `paired`: the launch shares the chip with a second one (a batch's lanes);
 // `xch`: exchange flavour.
 int plan_strip(long long nodes, int ny, int tiles_x, int storage, int req, bool paired = false, bool xch = false);

@@ -65,8 +65,7 @@ __host__ __device__ constexpr int two_cols(bool yper) { return 64 - 2 * two_halo
 // rows and columns a step leaves incomplete on either side are one for its
 // first half (the colour field's neighbours) and one for the pull of the next;
 // a ghost row beyond a wall is formed from its neighbour columns, one more.
-constexpr int kTileRows = 16;
-__host__ __device__ constexpr int tile_out(int T) { return kTileRows - 2 * (2 * T - 1); }
+__host__ __device__ constexpr int tile_out(int T, int rows) { return rows - 2 * (2 * T - 1); }
 __host__ __device__ constexpr int tile_halo(int T, bool yper) { return yper ? 2 * T - 1 : 3 * T - 1; }
 __host__ __device__ constexpr int tile_cols(int T, bool yper) { return 64 - 2 * tile_halo(T, yper); }
 

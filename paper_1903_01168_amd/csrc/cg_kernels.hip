@@ -1056,25 +1056,26 @@ __device__ __forceinline__ void step_two(const SlotDesc *__restrict__ slots, int
 // T fused time steps of a lattice that does not fill the chip (FP32 storage).
 // One step of it takes the launch, two waits for memory and a row of
 // arithmetic at the rate of few wavefronts, whatever its size; here T steps
-// share the first two.  A workgroup of 16 wavefronts holds one row of 64
+// share the first two.  A workgroup of W wavefronts holds one row of 64
 // columns in each, and its state between steps in LDS (18 words per node): per
 // step every wavefront pulls its row, shares its colour field (and Q),
 // collides with those of the rows on either side and puts what it has.  Rows
 // and columns whose neighbours the workgroup does not hold drop out step by
 // step: of 16 x 64 nodes 6 x 54 (48 between walls) are left after three steps,
-// 10 x 58 (54) after two.  The nodes' arithmetic is the single step's, to the
-// bit.
+// 10 x 58 (54) after two, of 12 x 64 2 x 54 after three.  The nodes'
+// arithmetic is the single step's, to the bit.
 //
 // The wavefronts' registers and LDS fill a CU.  Measured, us per step, single
-// steps before against this: 64^2 4.9 -> 3.7, 100^2 with wetting walls and
-// correction 5.5 -> 4.1, 300 x 200 6.8 -> 4.05 (T = 3), 512^2 11.6 -> 9.5 (T =
-// 2).  What bounds it: the arithmetic of a row, 480 vector instructions a step
-// from four, then three, then two wavefronts a SIMD (2.5, 1.9 and 1.6 us), and
-// 5 us of launch and memory latency.
-template <int T, bool NSC>
+// steps before against this: 64^2 4.9 -> 3.15, 100^2 with wetting walls and
+// correction 5.5 -> 3.5 (T = 3, W = 12), 300 x 200 6.8 -> 4.05 (3, 16), 512^2
+// 11.6 -> 9.5 (2, 16).  What bounds it: the arithmetic of a row, 480 vector
+// instructions a step from W / 4 wavefronts a SIMD, then one less with each
+// step (2.5, 1.9 and 1.6 us from four, three and two), and 5 us of launch and
+// memory latency.
+template <int T, int W, bool NSC>
 __device__ __forceinline__ void step_tile(const SlotDesc *__restrict__ slots, int nslots, int total_tiles, int parity)
 {
-    constexpr int ST = ST_F32, W = kTileRows;
+    constexpr int ST = ST_F32;
     __shared__ float pops[W * 18 * 64 + 2];
     __shared__ float field[W * 64], fqx[NSC ? W * 64 : 1], fqy[NSC ? W * 64 : 1];
 
@@ -1102,7 +1103,7 @@ __device__ __forceinline__ void step_tile(const SlotDesc *__restrict__ slots, in
     const Halves src = halves<ST>(S, parity ? S.buf[1] : S.buf[0]);
     const Halves dst = halves<ST>(S, parity ? S.buf[0] : S.buf[1]);
 
-    const int yl = tyi * tile_out(T) - (2 * T - 1) + w;   // the wavefront's row
+    const int yl = tyi * tile_out(T, W) - (2 * T - 1) + w;   // the wavefront's row
     const bool row = yper || (yl >= 0 && yl < ny);
     const int y = yper ? wrap_near(yl, ny) : yl;
     const bool wlo = !yper && yl == 0, whi = !yper && yl == ny - 1;
@@ -1223,11 +1224,11 @@ k_step(const SlotDesc *__restrict__ slots, int nslots, int total_tiles, int pari
     step_any<ST, W, KV>(slots, nslots, total_tiles, parity, launch_idx);
 }
 
-template <int T, bool NSC>
-__global__ void __launch_bounds__(64 * kTileRows) __attribute__((amdgpu_waves_per_eu(4, 4)))
+template <int T, int W, bool NSC>
+__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W / 4, W / 4)))
 k_step_tile(const SlotDesc *__restrict__ slots, int nslots, int total_tiles, int parity)
 {
-    step_tile<T, NSC>(slots, nslots, total_tiles, parity);
+    step_tile<T, W, NSC>(slots, nslots, total_tiles, parity);
 }
 
 template <int W>
@@ -1472,8 +1473,12 @@ static hipError_t step_two_tx(int tx, const SlotDesc *d, int nslots, int tiles, 
 template <int ST, int T, bool NSC>
 static hipError_t step_tile_v(int tx, const SlotDesc *d, int nslots, int tiles, int parity, hipStream_t s)
 {
-    if (ST != ST_F32 || tx != 64 * kTileRows) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_step_tile<T, NSC>), dim3(tiles), dim3(tx), 0, s, d, nslots, tiles, parity);
+    if (ST != ST_F32) return hipErrorInvalidValue;
+    if (tx == 1024)
+        hipLaunchKernelGGL((k_step_tile<T, 16, NSC>), dim3(tiles), dim3(1024), 0, s, d, nslots, tiles, parity);
+    else if (tx == 768 && T == 3)
+        hipLaunchKernelGGL((k_step_tile<3, 12, NSC>), dim3(tiles), dim3(768), 0, s, d, nslots, tiles, parity);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

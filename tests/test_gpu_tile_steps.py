@@ -27,8 +27,8 @@ def _lattice(nx, ny, bc_x, bc_y, nsc):
     return g
 
 
-# around the 54 (48 between walls) columns and 6 rows of a workgroup of three steps, narrower and flatter than it,
-# and the largest of one round of workgroups; two steps in one round and in two; just beyond
+# around the 54 (48 between walls) columns and 2 or 6 rows of a workgroup of three steps, narrower and flatter than
+# it, and the largest of one round of workgroups; two steps in one round and in two; just beyond
 SHAPES = [(64, 64), (54, 6), (55, 7), (47, 95), (49, 13), (7, 5), (2, 30), (97, 4), (33, 5), (300, 200), (2592, 25),
           (319, 321), (59, 1201), (512, 512), (647, 290), (541, 520)]
 
