@@ -226,8 +226,8 @@ void *lbm_stream(const lbm_ctx *ctx);
 
 /* ---- batched stepping -------------------------------------------------
  * A batch advances several contexts (same device, same storage type) with one
- * kernel launch per group of lattices and time step (FP32 groups with 500 000
- * nodes and more in flight: per two time steps): every workgroup finds
+ * kernel launch per group of lattices and time step (FP32 groups that keep
+ * few CUs busy, or have 500 000 nodes and more in flight: per two time steps): every workgroup finds
  * its lattice in a device table of lattice descriptors.  A batch of two or more lattices is split
  * into groups (contiguous, balanced by bytes, at least two, never mixing
  * kernel variants) sized so that two groups fit MI355X's 256 MB Infinity

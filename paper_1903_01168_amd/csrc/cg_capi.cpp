@@ -352,8 +352,8 @@ int plan_tile(const lbm_params *p, int variant, int &rows)
     }
     rows = 16;
     tile_grid(p, 2, rows, tx, ty);
-    if ((long long)tx * ty <= 256) return 2;
-    return (long long)tx * ty <= 512 && (long long)p->nx * p->ny >= 180000 ? 2 : 0;
+    const long long tiles = (long long)tx * ty;
+    return tiles <= 256 || (tiles <= 512 && (long long)p->nx * p->ny >= 180000) ? 2 : 0;
 }
 
 void set_geometry(SlotDesc &d, const lbm_params *p, const Layout &L, int tx, int strip, bool xch, bool two)
@@ -898,9 +898,10 @@ struct BatchGroup {
     long long nodes = 0;
     int variant = 0;                    // step-kernel variant of its launches (one per group, KV_XCH included)
     int tx = 0;                         // threads per workgroup
-    // two steps per launch (KV_TWO) wherever a turn has enough of them: its
-    // own table of lattice descriptors, behind the other one
-    bool two = false;
+    // two steps per launch (kernel variant `two`: KV_TWO, KV_TILE; 0: no)
+    // wherever a turn has enough of them: its own table of lattice
+    // descriptors, behind the other one
+    int two = 0;
     std::vector<SlotDesc> slots2;
     int tiles2 = 0, tx2 = 0;
     hipGraphExec_t graph[2] = {nullptr, nullptr};
@@ -983,21 +984,28 @@ int lbm_batch_create(lbm_ctx *const *ctxs, int32_t n, int32_t tile_x, void *hip_
     // strips are planned for what shares the chip: the group, and the group
     // the other lane steps beside it (two groups of the batch at a time)
     long long pair_nodes = 0, pair_rows = 0;   // pair_rows: wavefronts across times rows, two-step launches
+    long long pair_tiles = 0;                  // workgroups of two-step launches that hold their rows
     {
-        std::vector<long long> gn, gr;
+        std::vector<long long> gn, gr, gt;
         for (int gi = 0; gi < ngroups; ++gi) {
-            long long nodes = 0, rows = 0;
+            long long nodes = 0, rows = 0, tiles = 0;
             for (int i = first[gi]; i < first[gi + 1]; ++i) {
+                int tx, ty;
+                tile_grid(&ctxs[i]->p, 2, 16, tx, ty);
+                tiles += (long long)tx * ty;
                 nodes += (long long)ctxs[i]->p.nx * ctxs[i]->p.ny;
                 rows += (long long)two_waves(&ctxs[i]->p) * ctxs[i]->p.ny;
             }
             gn.push_back(nodes);
             gr.push_back(rows);
+            gt.push_back(tiles);
         }
         std::sort(gn.begin(), gn.end());
         std::sort(gr.begin(), gr.end());
+        std::sort(gt.begin(), gt.end());
         pair_nodes = gn.back() + (ngroups > 1 ? gn[ngroups - 2] : 0);
         pair_rows = gr.back() + (ngroups > 1 ? gr[ngroups - 2] : 0);
+        pair_tiles = gt.back() + (ngroups > 1 ? gt[ngroups - 2] : 0);
     }
     for (int gi = 0; gi < ngroups; ++gi) {
         BatchGroup &G = b->groups[gi];
@@ -1016,16 +1024,33 @@ int lbm_batch_create(lbm_ctx *const *ctxs, int32_t n, int32_t tile_x, void *hip_
         G.variant = gp.variant;
         const bool xch = gp.variant & cgd::KV_XCH;
         int min_ny = INT_MAX;
-        for (int i = first[gi]; i < first[gi + 1]; ++i) min_ny = std::min(min_ny, ctxs[i]->p.ny);
-        G.two = plan_two(pair_nodes, b->storage, kind[first[gi]], min_ny);
-        G.tx2 = two_tx(min_nx, tile_x);
+        bool shape_req = tile_x != 0;
+        for (int i = first[gi]; i < first[gi + 1]; ++i) {
+            min_ny = std::min(min_ny, ctxs[i]->p.ny);
+            shape_req = shape_req || ctxs[i]->strip_req != 0;
+        }
+        // two steps per launch, one row per wavefront (see plan_tile): where
+        // all workgroups in flight have a CU, or hold 380 nodes of their 580
+        // (nine n^2 lattices, us per step, one step a launch against two: 96
+        // 8.2 / 6.6, 112 9.0 / 6.7, 144 11.7 / 8.3, 176 13.3 / 12.8, 208 16.0
+        // / 14.3); from 500 000 nodes plan_two's launches are faster
+        const bool tile = !shape_req && min_ny >= 4 && b->storage == LBM_STORE_F32 && !(kind[first[gi]] & cgd::KV_ISO) &&
+                          pair_nodes < 500000 && (pair_tiles <= 256 || pair_nodes >= 380 * pair_tiles);
+        G.two = tile ? cgd::KV_TILE | cgd::KV_TWO | kind[first[gi]]
+                     : (plan_two(pair_nodes, b->storage, kind[first[gi]], min_ny) ? (int)cgd::KV_TWO : 0);
+        G.tx2 = tile ? 64 * 16 : two_tx(min_nx, tile_x);
         long long tiles2 = 0;
         for (int i = first[gi]; i < first[gi + 1]; ++i) {
             lbm_ctx *c = ctxs[i];
             if (G.two) {
                 SlotDesc d = c->desc;
-                set_geometry(d, &c->p, c->lay, G.tx2,
-                             plan_two_strip(&c->p, pair_nodes, pair_rows, c->strip_req), false, true);
+                if (tile) {
+                    d.strip = cgd::tile_out(2, 16);
+                    tile_grid(&c->p, 2, 16, d.tiles_x, d.tiles_y);
+                } else {
+                    set_geometry(d, &c->p, c->lay, G.tx2,
+                                 plan_two_strip(&c->p, pair_nodes, pair_rows, c->strip_req), false, true);
+                }
                 d.tile_begin = (int)tiles2;
                 d.active_steps = INT_MAX;
                 if (c->steps & 1) std::swap(d.buf[0], d.buf[1]);
@@ -1100,7 +1125,7 @@ int lbm_batch_create(lbm_ctx *const *ctxs, int32_t n, int32_t tile_x, void *hip_
 static hipError_t group_launch(lbm_batch *b, BatchGroup &G, bool two, int par, hipStream_t s)
 {
     const int n = (int)G.slots.size();
-    if (two) return cgd::launch_step(b->storage, G.tx2, G.d_slots + n, n, G.tiles2, par, 0, s, cgd::KV_TWO);
+    if (two) return cgd::launch_step(b->storage, G.tx2, G.d_slots + n, n, G.tiles2, par, 0, s, G.two);
     return cgd::launch_step(b->storage, G.tx, G.d_slots, n, G.tiles, par, 0, s, G.variant);
 }
 

@@ -54,3 +54,24 @@ def test_any_number_of_steps_bit_identical():
             b.step(n)
         assert a.steps_done == b.steps_done == 167
         assert a.get_pops().tobytes() == b.get_pops().tobytes()
+
+
+@pytest.mark.parametrize("n,nsc", [(3, False), (5, True), (9, False)])
+def test_batch_tile_steps_bit_identical(n, nsc):
+    """Batches of small lattices, two groups in flight: pairs of two-step launches, single steps for the rest."""
+    kinds = [("periodic", "periodic"), ("open", "freeslip"), ("periodic", "walls"), ("open", "slip_top")]
+    args = [(61 + 23 * k, 40 + 17 * k) + kinds[k % 4] + (nsc,) for k in range(n)]
+    alone, mixed = [_lattice(*a) for a in args], [_lattice(*a) for a in args]
+    mixed[0].step(1)
+    alone[0].step(1)
+    b = capi.Batch(mixed)
+    b.step(75)
+    b.step(2)
+    for g in alone:
+        for _ in range(77):
+            g.step(1)
+    for g, m in zip(alone, mixed):
+        assert g.get_pops().tobytes() == m.get_pops().tobytes()
+    b.close()
+    for g in alone + mixed:
+        g.close()
